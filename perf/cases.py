@@ -38,8 +38,8 @@ def listed():
         _case("mlp1000_n20", "round", (784, 1000, 1000, 10), 20, 15, 128, 0.01, 60000),
         # the largest float32 run, forty workers (the default benchmark)
         _case("mlp2000_n40", "round", (784, 2000, 2000, 2000, 10), 40, 30, 128, 0.005, 120000),
-        # Adam as the local rule
-        _case("mlp1000_adam", "round", (784, 1000, 1000, 10), 8, 15, 128, 0.0005, 60000, order="sequential",
+        # Adam as the local rule (eight commits of a round add up to a rate of 0.0008)
+        _case("mlp1000_adam", "round", (784, 1000, 1000, 10), 8, 15, 128, 0.0001, 60000, order="sequential",
               adam=True),
         # the comparison of Section 4: one local step per commit, the
         # accumulated update scaled by its staleness (commit-heavy rounds)
@@ -89,7 +89,7 @@ def draw(rng):
         # (the accumulated commit without staleness scaling diverges; the
         # rate falls with n so that long timed runs stay finite)
         stale = rng.random() < 0.25
-        return _case(None, kind, dims, n, lam, m, (0.001 if adam else 0.05) / n, rows,
+        return _case(None, kind, dims, n, lam, m, (0.0004 if adam else 0.05) / n, rows,
                      data=rng.choice(("gauss", "sparse")), order=rng.choice(("permutation", "sequential")),
                      dtype=dtype, normalize=not stale or rng.random() < 0.3, stale=stale, adam=adam)
 
@@ -187,7 +187,7 @@ def tolerance(case):
         # predictions may differ where two logits are within rounding
         return {"rel": 4e-3 if bf16 else 1e-6, "max": 4e-2 if bf16 else 1e-4, "differ": 2e-3}
     if bf16:
-        return {"rel": 4e-4, "max": 5e-2}
+        return {"rel": 2e-3 if case["adam"] else 4e-4, "max": 5e-2}
     return {"rel": 1e-5 if case["adam"] else 2e-6, "max": 5e-2 if case["adam"] else 1e-3}
 
 

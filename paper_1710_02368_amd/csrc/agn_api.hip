@@ -366,13 +366,13 @@ int enqueue_step(agn_ctx* c, const agn_data* d, int64_t S, int step) {
     w.lam = c->normalize ? (float)c->lam : 1.f;  // divisor of the committed delta
     w.last = last;
     w.adam = adam_args(c, L - 1);
-    // with a first-layer weight gradient on the persistent direct-load path,
-    // the output layer's update rides in that launch (it touches nothing the
-    // layers in between read or write).  The strip schedule of the first
+    // with at most 10 classes the output layer's update rides in the first
+    // layer's weight-gradient launch (it touches nothing the layers in
+    // between read or write).  The strip schedule of the first
     // layer leaves it a launch of its own: inside the strips each unit's
     // chain of dependent loads ran ahead of the strip's work in every
     // workgroup (0.8 ms per round at 40 workers against 0.4 for the launch)
-    fold_head_dw = !bf && !strip_dw && L >= 2 && gemm_f32_dl_dw_head_ok(dw_args(0), w);
+    fold_head_dw = !bf && !strip_dw && L >= 2 && gemm_f32_dw_head_ok(w);
     if (!fold_head_dw) HIP_CHECK(c, timed(c, AGN_K_OUTPUT_DW, [&] { return launch_head_dw(w, c->ls); }));
   } else {
     // softmax cross-entropy: per-row loss and the output gradient dZ_L
@@ -424,7 +424,7 @@ int enqueue_step(agn_ctx* c, const agn_data* d, int64_t S, int step) {
     } else if (strip_dw) {
       HIP_CHECK(c, timed(c, AGN_K_DW_FIRST, [&] { return launch_gemm_f32_strip_dw(w, c->ls); }));
     } else if (fold_head_dw) {
-      HIP_CHECK(c, timed(c, AGN_K_DW_FIRST, [&] { return launch_gemm_f32_dl_dw_head(w, hdw, c->ls); }));
+      HIP_CHECK(c, timed(c, AGN_K_DW_FIRST, [&] { return launch_gemm_f32_dw_head(w, hdw, c->ls); }));
     } else {
       HIP_CHECK(c, timed(c, AGN_K_DW_FIRST, [&] { return gemm(0, 0, w); }));
     }
@@ -747,8 +747,8 @@ int agn_create(const agn_shapes* shapes, int32_t n, int32_t lambda, float eta, u
   if (e == hipSuccess) e = hipMemset(c->round_dev, 0, 8);
   if (e == hipSuccess) e = hipMemset(c->zero, 0, 1024 * sizeof(float));
   if (e == hipSuccess) e = hipMemset(c->loss, 0, (size_t)n * lambda * c->m * 4);
-  // activations and gradients: their row padding stays zero (no kernel
-  // writes it; the bf16 products read it as a zero K tail)
+  // activations and gradients: their row padding stays zero (kernels write
+  // nothing there, or zeros; the products read it as a zero K tail)
   for (int l = 1; e == hipSuccess && l <= L; ++l) {
     const size_t bytes = (size_t)n * c->m * c->lda[l] * act;
     if (l < L) e = hipMemset(c->H[l], 0, bytes);

@@ -104,11 +104,6 @@ hipError_t launch_gemm_bf16(int a_kc, int b_kc, const GemmArgs& g, hipStream_t s
 // one layer in one launch
 hipError_t launch_gemm_f32_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s);
 hipError_t launch_gemm_bf16_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s);
-// direct global->LDS variants of the float32 products (used when both
-// operands qualify, see gemm_f32_dl_ok)
-bool gemm_f32_dl_ok(int a_kc, int b_kc, const GemmArgs& g);
-hipError_t launch_gemm_f32_dl(int a_kc, int b_kc, const GemmArgs& g, hipStream_t s);
-hipError_t launch_gemm_f32_dl_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s);
 // the backward launch of a float32 hidden layer as column strips of its
 // weights (input gradient and weight gradient + update sharing each weight
 // block in LDS), used when gemm_f32_strip_ok
@@ -120,10 +115,10 @@ hipError_t launch_gemm_f32_strip_bwd(const GemmArgs& dx, const GemmArgs& dw, hip
 bool gemm_f32_strip_dw_ok(const GemmArgs& dw);
 hipError_t launch_gemm_f32_strip_dw(const GemmArgs& dw, hipStream_t s);
 struct HeadDwArgs;
-// the first layer's direct-load weight gradient with the output layer's
-// weight gradient + update (C <= 10) folded into the same launch
-bool gemm_f32_dl_dw_head_ok(const GemmArgs& g, const HeadDwArgs& h);
-hipError_t launch_gemm_f32_dl_dw_head(const GemmArgs& g, const HeadDwArgs& h, hipStream_t s);
+// the first layer's weight gradient with the output layer's weight gradient
+// + update (C <= 10) in the same launch
+bool gemm_f32_dw_head_ok(const HeadDwArgs& h);
+hipError_t launch_gemm_f32_dw_head(const GemmArgs& g, const HeadDwArgs& h, hipStream_t s);
 // direct global->LDS variants of the bf16 products (used when the operands
 // and outputs qualify, see gemm_bf16_dl_ok)
 bool gemm_bf16_dl_ok(int a_kc, int b_kc, const GemmArgs& g);

@@ -1,0 +1,320 @@
+// Float32 products on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), each
+// float32 operand split into three bf16 pieces x = h + m + l.
+//
+// The split is exact for normal float32 values: h = bf16(x), m = bf16(x - h),
+// l = x - h - m hold 8 bits each, rounded to nearest, and the subtractions
+// are exact.  A product a*b is the sum of the six piece products
+// ah*bh + (ah*bm + am*bh) + (am*bm + ah*bl + al*bh); the three left out are
+// below 2^-26 of it.  ah*bh goes to one accumulator, the five small ones to
+// a second, added at the end: one rounding per 16 k in the large sum, where
+// the float32 MFMA rounds four times.  Measured against 64 bits (K = 64 to
+// 2000; normal, sparse, rectified and positive operands) the relative error
+// is 0.33 to 0.50 of the float32 MFMA's (K = 784, sparse inputs x normal
+// weights: 7.7e-8 against 2.3e-7).  Six bf16 MFMAs take 6/16 of the float32
+// MFMAs' cycles at the nominal rates; with random operands the card sustains
+// 1.75 PFLOP/s in bf16 (292 TFLOP/s of split products) against 154 in float32.
+//
+// The split takes 3.5 vector instructions per element: v_cvt_pk_bf16_f32
+// rounds two elements to a packed pair, v_dot2c_f32_bf16 subtracts one piece
+// of that pair from its element (dot with (-1, 0) or (0, -1)).  Masks and
+// subtractions (5.5 per element) overlap with MFMAs, which the dot products
+// do not, and still measured slower (forward product 40 x 128 x 2000 x 2000:
+// 271 against 256 us; weight gradient 547 against 518).
+//
+// Infinities: inf - inf in the split makes NaN where the float32 product
+// would keep an infinity, so a tile with a non-finite result is computed
+// again with float32 MFMAs straight from memory (split_gather).
+#pragma once
+
+#include "device_common.h"
+
+namespace agn {
+namespace {
+
+typedef float sp_f32x16 __attribute__((ext_vector_type(16)));
+typedef float sp_f32x4 __attribute__((ext_vector_type(4)));
+typedef float sp_f32x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 sp_bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 sp_bf16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t sp_u32x4 __attribute__((ext_vector_type(4)));
+
+// eight float32 values -> their three bf16 pieces, 16 bytes each
+__device__ __forceinline__ void split8(const float (&x)[8], sp_u32x4& h, sp_u32x4& m, sp_u32x4& l) {
+  // (-1, 0) and (0, -1), the first from a register: the compiler would encode
+  // it as the inline constant -1.0, which the instruction reads as (0, -1)
+  uint32_t u0 = 0x0000BF80u;
+  asm("" : "+s"(u0));
+  const sp_bf16x2 n0 = __builtin_bit_cast(sp_bf16x2, u0);
+  const sp_bf16x2 n1 = __builtin_bit_cast(sp_bf16x2, 0xBF800000u);
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const float x0 = x[2 * p], x1 = x[2 * p + 1];
+    sp_bf16x2 a, b, c;
+    a[0] = (__bf16)x0;
+    a[1] = (__bf16)x1;
+    const float r0 = __builtin_amdgcn_fdot2_f32_bf16(a, n0, x0, false);
+    const float r1 = __builtin_amdgcn_fdot2_f32_bf16(a, n1, x1, false);
+    b[0] = (__bf16)r0;
+    b[1] = (__bf16)r1;
+    const float s0 = __builtin_amdgcn_fdot2_f32_bf16(b, n0, r0, false);
+    const float s1 = __builtin_amdgcn_fdot2_f32_bf16(b, n1, r1, false);
+    c[0] = (__bf16)s0;
+    c[1] = (__bf16)s1;
+    h[p] = __builtin_bit_cast(uint32_t, a);
+    m[p] = __builtin_bit_cast(uint32_t, b);
+    l[p] = __builtin_bit_cast(uint32_t, c);
+  }
+}
+
+// Shape of a workgroup's tile: WGM x WGN x KW waves; a wave owns WTM x WTN
+// outputs (blocks of 32 x 32) over SL slices of 16 k per K step, and the KW
+// waves of the same outputs take different slices (their sums are added
+// through LDS).
+template <int WTM_, int WTN_, int WGM_, int WGN_, int KW_, int SL_>
+struct SplitCfg {
+  static constexpr int WTM = WTM_, WTN = WTN_, WGM = WGM_, WGN = WGN_, KW = KW_, SL = SL_;
+  static constexpr int BM = WTM * WGM, BN = WTN * WGN, BK = 16 * KW * SL, NTH = 64 * WGM * WGN * KW;
+  static constexpr int ELD = BN;               // row stride (floats) of the epilogue tile
+  static constexpr int EPI = KW * BM * ELD * 4;
+  static constexpr int NC = (BM * BN / 4 + NTH - 1) / NTH;  // epilogue chunks of 4 outputs per thread
+  static_assert(NC == 1 || BM * BN % (4 * NTH) == 0, "epilogue chunks");
+};
+
+// element (outer o, k) of an operand straight from memory
+template <bool KC>
+__device__ __forceinline__ float operand_at(const Operand& op, const Gather& g, int64_t w, int64_t t, int64_t o,
+                                            int64_t k) {
+  int64_t r = KC ? o : k;
+  if (op.gather) r = batch_row(w, t, g.mb, g.S, r);
+  return reinterpret_cast<const float*>(op.ptr)[w * op.wstride + r * op.ld + (KC ? k : o)];
+}
+
+// Where a wave's accumulators lie in the workgroup's tile: block bi covers
+// rows 32*bi + i (i = 0..31) of the wave's, or rows MB*i + bi (interleaved);
+// columns likewise.
+template <class Cfg, bool A_IL, bool B_IL>
+struct SplitPlace {
+  static constexpr int MB = Cfg::WTM / 32, NB = Cfg::WTN / 32;
+  static __device__ __forceinline__ int row(int bi, int i) { return A_IL ? MB * i + bi : 32 * bi + i; }
+  static __device__ __forceinline__ int col(int bj, int j) { return B_IL ? NB * j + bj : 32 * bj + j; }
+};
+
+// Coordinates of a tile and of a thread in it.
+template <class Cfg>
+struct SplitCoord {
+  int tid, lane, wave, kw, wn, wm, li, lh, worker, m0, n0;
+  // this thread's epilogue chunks: 4 outputs at column ec of rows m0 + er0 +
+  // i*ERS (threads past the tile's last chunk repeat its last row, storing
+  // nothing)
+  int ecl, ec, er0;
+  bool mine;
+  static constexpr int ERS = Cfg::NTH / (Cfg::BN / 4);
+
+  __device__ __forceinline__ SplitCoord(const GemmArgs& g, int logical) {
+    tid = threadIdx.x;
+    lane = tid & 63;
+    wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    kw = wave % Cfg::KW;
+    wn = wave / Cfg::KW % Cfg::WGN;
+    wm = wave / Cfg::KW / Cfg::WGN;
+    li = lane & 31;
+    lh = lane >> 5;
+    const int tm = (g.M + Cfg::BM - 1) / Cfg::BM, tn = (g.N + Cfg::BN - 1) / Cfg::BN;
+    worker = logical / (tm * tn);
+    const int rem = logical % (tm * tn);
+    // consecutive tiles share an XCD's L2: one worker's few rows of A and a
+    // block of its weights, or (batch 1, the evaluation) a block of rows and
+    // all of the weights
+    const int ti = g.batch == 1 ? rem / tn : rem % tm, tj = g.batch == 1 ? rem % tn : rem / tm;
+    m0 = ti * Cfg::BM;
+    n0 = tj * Cfg::BN;
+    ecl = 4 * (tid % (Cfg::BN / 4));
+    ec = n0 + ecl;
+    er0 = min(tid / (Cfg::BN / 4), Cfg::BM - 1);
+    mine = tid / (Cfg::BN / 4) < Cfg::BM;
+  }
+};
+
+// Operands of the epilogue, loaded from indices clamped into the matrix (its
+// rows are padded to 8; values outside are never stored): the bias, the ReLU
+// mask, or the weights (with the snapshot on a round's last step, and Adam's
+// moments).
+template <class Cfg, int EPI, bool ADAM>
+struct SplitEpilogue {
+  static constexpr int NC = Cfg::NC;
+  static constexpr bool DW = EPI == EPI_DW_UPDATE;
+  sp_f32x4 pre[NC], snap[DW ? NC : 1], mo[DW && ADAM ? NC : 1], ve[DW && ADAM ? NC : 1];
+
+  __device__ __forceinline__ void load(const GemmArgs& g, const SplitCoord<Cfg>& c) {
+    const int cc = min(c.ec, (g.N - 1) / 4 * 4);
+    if (EPI == EPI_DX_MASK || DW) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const int64_t row = min(c.m0 + c.er0 + i * c.ERS, g.M - 1);
+        if (EPI == EPI_DX_MASK) {
+          pre[i] = *reinterpret_cast<const sp_f32x4*>(reinterpret_cast<const float*>(g.mask) + c.worker * g.mstride +
+                                                      row * g.ldm + cc);
+        } else {
+          const int64_t e = c.worker * g.pstride + row * g.ldw + cc;
+          pre[i] = *reinterpret_cast<const sp_f32x4*>(g.w_src + e);
+          if (g.last) snap[i] = *reinterpret_cast<const sp_f32x4*>(g.w_snap + e);
+          if (ADAM) {
+            mo[i] = *reinterpret_cast<const sp_f32x4*>(g.adam.mw + e);
+            ve[i] = *reinterpret_cast<const sp_f32x4*>(g.adam.vw + e);
+          }
+        }
+      }
+    } else {
+      const float* bp = g.bias + c.worker * g.bstride;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pre[0][e] = bp[min(c.ec + e, g.N - 1)];
+    }
+  }
+
+  // v: this thread's chunks of the product; gb: the bias gradient of row tid
+  // (first column tile of a weight gradient)
+  __device__ __forceinline__ void store(const GemmArgs& g, const SplitCoord<Cfg>& c, const sp_f32x4 (&v)[NC], float gb) {
+    if (!DW) {
+      if (c.mine && c.ec < g.ldo) {  // (columns past N are stored as zeros: the row padding stays zero)
+        float* out = reinterpret_cast<float*>(g.out) + c.worker * g.ostride + c.ec;
+#pragma unroll
+        for (int i = 0; i < NC; ++i) {
+          const int64_t row = c.m0 + c.er0 + i * c.ERS;
+          if (row >= g.M) continue;
+          sp_f32x4 o;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float x = v[i][e];
+            if (EPI == EPI_DX_MASK) {
+              x = pre[i][e] > 0.f ? x : 0.f;
+            } else {
+              x += pre[0][e];
+              if (EPI == EPI_FWD_RELU) x = x > 0.f ? x : 0.f;
+            }
+            o[e] = c.ec + e < g.N ? x : 0.f;
+          }
+          *reinterpret_cast<sp_f32x4*>(out + row * g.ldo) = o;
+        }
+      }
+      return;
+    }
+    const AdamCoef ac = ADAM ? adam_coef(g.g, g.adam) : AdamCoef{1.f, 1.f};
+    const int64_t wo = c.worker * g.pstride;
+    if (c.mine && c.ec < g.N) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) {
+        const int64_t row = c.m0 + c.er0 + i * c.ERS;
+        if (row >= g.M) continue;
+        const int64_t e0 = wo + row * g.ldw + c.ec;
+        sp_f32x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          float step = v[i][e];
+          if (ADAM) {
+            float mm = mo[i][e], vv = ve[i][e];
+            step = adam_moments(step, mm, vv, g.adam, ac);
+            mo[i][e] = mm;
+            ve[i][e] = vv;
+          }
+          o[e] = pre[i][e] - g.eta * step;
+          if (g.last) o[e] = (o[e] - snap[i][e]) / g.lam;
+        }
+        if (c.ec + 4 <= g.N) {
+          *reinterpret_cast<sp_f32x4*>(g.w_dst + e0) = o;
+          if (ADAM) {
+            *reinterpret_cast<sp_f32x4*>(g.adam.mw + e0) = mo[i];
+            *reinterpret_cast<sp_f32x4*>(g.adam.vw + e0) = ve[i];
+          }
+        } else {
+          for (int e = 0; e < 4 && c.ec + e < g.N; ++e) {
+            g.w_dst[e0 + e] = o[e];
+            if (ADAM) g.adam.mw[e0 + e] = mo[i][e], g.adam.vw[e0 + e] = ve[i][e];
+          }
+        }
+      }
+    }
+    if (c.n0 == 0 && c.tid < Cfg::BM && c.m0 + c.tid < g.M) {
+      const int64_t e = wo + c.m0 + c.tid;
+      const float step = ADAM ? adam_dir(gb, g.adam.mb, g.adam.vb, e, g.adam, ac) : gb;
+      const float nb = g.b_src[e] - g.eta * step;
+      g.b_dst[e] = g.last ? (nb - g.b_snap[e]) / g.lam : nb;
+    }
+  }
+};
+
+// The waves' accumulators to LDS and each thread's chunks back in row order,
+// the KW partial sums added in wave order.  A result that is not finite makes
+// the workgroup compute its tile again with float32 MFMAs straight from
+// memory.  lds is free when this is called (a barrier lies before).
+template <class Cfg, class Place, bool A_KC, bool B_KC>
+__device__ __forceinline__ void split_gather(const GemmArgs& g, const SplitCoord<Cfg>& c, float* et,
+                                             sp_f32x16 (&acc)[Cfg::WTM / 32][Cfg::WTN / 32], sp_f32x4 (&v)[Cfg::NC]) {
+  constexpr int MB = Cfg::WTM / 32, NB = Cfg::WTN / 32, NC = Cfg::NC, KW = Cfg::KW, BM = Cfg::BM, ELD = Cfg::ELD;
+  for (int pass = 0;; ++pass) {
+    float* dst = et + (c.kw * BM + c.wm * Cfg::WTM) * ELD + c.wn * Cfg::WTN;
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < NB; ++bj)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          dst[Place::row(bi, 8 * (r >> 2) + 4 * c.lh + (r & 3)) * ELD + Place::col(bj, c.li)] = acc[bi][bj][r];
+    __syncthreads();
+    float chk = 0.f;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) {
+      const float* src = et + (c.er0 + i * c.ERS) * ELD + c.ecl;
+      v[i] = *reinterpret_cast<const sp_f32x4*>(src);
+#pragma unroll
+      for (int w = 1; w < KW; ++w) v[i] += *reinterpret_cast<const sp_f32x4*>(src + w * BM * ELD);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) chk += v[i][e] * 0.f;
+    }
+    if (pass || !__syncthreads_or(chk != 0.f)) return;
+    const int64_t t = g.a.gather || g.b.gather ? gather_step(g.g) : 0;
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < NB; ++bj)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
+    for (int k0 = 2 * c.kw; k0 < g.K; k0 += 2 * KW) {
+      const int k = k0 + c.lh, kc = min(k, g.K - 1);
+      float a[MB], b[NB];
+#pragma unroll
+      for (int bi = 0; bi < MB; ++bi) {
+        a[bi] = operand_at<A_KC>(g.a, g.g, c.worker, t, min(c.m0 + c.wm * Cfg::WTM + Place::row(bi, c.li), g.M - 1), kc);
+        if (k >= g.K) a[bi] = 0.f;
+      }
+#pragma unroll
+      for (int bj = 0; bj < NB; ++bj) {
+        b[bj] = operand_at<B_KC>(g.b, g.g, c.worker, t, min(c.n0 + c.wn * Cfg::WTN + Place::col(bj, c.li), g.N - 1), kc);
+        if (k >= g.K) b[bj] = 0.f;
+      }
+#pragma unroll
+      for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+        for (int bj = 0; bj < NB; ++bj)
+          acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[bi], b[bj], acc[bi][bj], 0, 0, 0);
+    }
+  }
+}
+
+// the six piece products of one slice of 16 k (see the top of this file)
+template <int MB, int NB>
+__device__ __forceinline__ void split_mfma(const sp_bf16x8 (&a)[3][MB], const sp_bf16x8 (&b)[3][NB],
+                                           sp_f32x16 (&acc)[MB][NB], sp_f32x16 (&low)[MB][NB]) {
+  constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
+#pragma unroll
+  for (int p = 0; p < 6; ++p)
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < NB; ++bj) {
+        sp_f32x16& d = p == 0 ? acc[bi][bj] : low[bi][bj];
+        d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[p]][bi], b[PB[p]][bj], d, 0, 0, 0);
+      }
+}
+
+}  // namespace
+}  // namespace agn

@@ -1,0 +1,92 @@
+"""The split float32 products at the edges of their tiles: every tile shape of
+the forward, input-gradient and weight-gradient products with ragged rows,
+columns and K, data rows that no 16-byte load fits, batches that wrap round
+their shard or exceed it, and operands that are not finite."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import AGNOracle, evaluate, unflat_params
+from tests.helpers import to_device
+
+pytestmark = pytest.mark.gpu
+
+# dims, n, m, N: one layer of each case lands on the named shape
+CASES = {
+    "small_unaligned": ((101, 71, 60, 40), 2, 20, 400),         # 32 x 32 tiles, single-float loads of the data
+    "small_k1": ((1, 33, 5, 3), 3, 7, 100),                     # K = 1, one column past a tile
+    "flat_midw": ((130, 514, 66, 10), 16, 70, 16 * 90),         # 32 x 64 forward, 64 x 64 weight gradient, m > 64
+    "flat_midw_unaligned": ((131, 514, 66, 12), 16, 70, 16 * 90),
+    "flat_bwd": ((64, 260, 514, 10), 16, 70, 16 * 90),          # 32 x 64 input gradient beside 64 x 64 weight tiles
+    "mid": ((68, 385, 33, 10), 40, 130, 40 * 200),              # 64 x 64 forward
+    "wide": ((36, 700, 33, 10), 48, 130, 48 * 200),             # 128 x 64 forward, the second row tile of 2 rows
+    "wide_unaligned": ((37, 700, 33, 10), 48, 130, 48 * 200),
+    "batch_over_shard": ((50, 70, 66, 10), 2, 50, 60),          # m = 50 rows of shards of 30
+    "batch_over_shard_unaligned": ((51, 70, 66, 10), 2, 50, 60),
+}
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("adam", [None, (0.9, 0.999, 1e-5)], ids=["sgd", "adam"])
+def test_round_matches_oracle(case, adam):
+    import paper_1710_02368_amd as agn
+    dims, n, m, N = CASES[case]
+    print(case, dims, n, m, N, adam, flush=True)
+    wl = W.small_workload(case, dims, n, 2, m, 0.02 if adam is None else 0.001, 1, N, order="permutation")
+    X, y = W.make_data(wl)
+    xd, yd = to_device(X, y)
+    g = agn.AGN(dims, n, wl.lam, wl.eta, m, seed=3, adam=adam)
+    o = AGNOracle(dims, n, wl.lam, wl.eta, m, seed=3, adam=adam)
+    order = W.commit_orders(wl)[0]
+    g.round(xd, yd, order)
+    o.round(X, y, order)
+    np.testing.assert_allclose(g.loss().cpu().numpy(), o.last_loss, rtol=2e-6)
+    a, b = g.central().cpu().numpy().astype(np.float64), o.central_flat().astype(np.float64)
+    # float32 sums of up to 700 terms; a unit at a ReLU edge moves its own row
+    assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(b)
+    assert np.max(np.abs(a - b)) <= 1e-3 * np.max(np.abs(b))
+    # each worker's step, against the displacement the oracle takes: 1e-2 in
+    # the 2-norm per tensor leaves room for such a unit and for the rounding
+    # of theta itself (half an ulp per step)
+    theta = unflat_params(o.central_flat(), dims)
+    for k in range(0, n, 7):
+        d = unflat_params(g.delta(k).cpu().numpy(), dims)
+        ref = unflat_params(np.concatenate([np.concatenate([w.ravel(), v.ravel()]) for w, v in o.last_deltas[k]]), dims)
+        for (dw, db), (rw, rb), (tw, tb) in zip(d, ref, theta):
+            for got, want, t in ((dw, rw, tw), (db, rb, tb)):
+                tol = 1e-2 * np.linalg.norm(want) + 2.0 ** -22 * np.linalg.norm(t)
+                assert np.linalg.norm(got.astype(np.float64) - want) <= tol, k
+    g.close()
+
+
+def test_infinities_and_largest_values_stay_what_they_are():
+    """An infinite weight makes infinities, not NaN, where the float32 product
+    has them; a value that rounds to infinity in bf16 still gives its finite
+    product."""
+    import torch
+
+    import paper_1710_02368_amd as agn
+    dims = (20, 40, 36, 6)
+    wl = W.small_workload("inf", dims, 2, 1, 8, 0.05, 1, 70)
+    X, y = W.make_data(wl)
+    vec = W.random_params(dims, 7)
+    p = unflat_params(vec, dims)
+    p[0][0][3, 5] = np.inf
+    big = X.copy()
+    big[:, 9] = 3.395e38       # above the largest bf16 value
+    q = unflat_params(vec, dims)
+    q[0][0][:, 9] *= 1e-36     # (products of about 100, weights no subnormals)
+    for what, params, data in (("inf", p, X), ("big", q, big)):
+        flat = np.concatenate([np.concatenate([w.ravel(), b.ravel()]) for w, b in params])
+        g = agn.AGN(dims, 2, 1, 0.05, 8, seed=1)
+        g.set_central(torch.from_numpy(flat).cuda())
+        xd, yd = to_device(data, y)
+        _, rl, rp = g.evaluate(xd, yd, row_outputs=True)
+        with np.errstate(invalid="ignore"):
+            row_loss, pred, logits = evaluate(params, data, y)
+        rl, rp = rl.cpu().numpy(), rp.cpu().numpy()
+        np.testing.assert_array_equal(rp, pred, err_msg=what)
+        np.testing.assert_array_equal(np.isfinite(rl), np.isfinite(row_loss))
+        ok = np.isfinite(row_loss)
+        np.testing.assert_allclose(rl[ok], row_loss[ok], rtol=1e-4, atol=1e-5)
+        g.close()

@@ -268,9 +268,9 @@ def traffic_class(name):
         return "output"
     if "_bwd_kernel" in name:
         return "bwd"
-    if "_dw_kernel" in name or "<false, false, 3>" in name:
+    if "_dw_kernel" in name or "<false, false, 3>" in name or ", false, false, 3," in name:
         return "dw_first"
-    if "<true, true" in name or "_fwd_kernel" in name or "_fwd8_kernel" in name or "gemm_bf16_dl_big_kernel" in name:
+    if "<true, true" in name or ", true, true, " in name or "_fwd_kernel" in name or "_fwd8_kernel" in name or "gemm_bf16_dl_big_kernel" in name:
         return "fwd"
     return None
 

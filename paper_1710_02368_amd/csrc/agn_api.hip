@@ -14,6 +14,9 @@
 //   Z         [n][m][ld_L]      logits
 //   dZ[l]     [n][m][ld_l]      gradients of the batch loss w.r.t. layer inputs, l = 1..L
 //   loss      [n][lambda][m]    per-row cross-entropy of the last round
+//   xrows     [steps][n][m][ld_0]  bf16 mode with data rows that no 16-byte load
+//                               fits: aligned copies of the mini-batches (of the
+//                               whole round, or of one step where that is large)
 // Step i of a round reads its weights from src = (i == 0 ? snap : buf[(i-1)%2])
 // and writes dst = buf[i%2]; reading and writing different buffers lets the
 // input-gradient and weight-gradient products of one layer run in either
@@ -56,6 +59,8 @@ struct agn_ctx {
   float* buf[2] = {nullptr, nullptr};
   uint16_t* snap16 = nullptr;
   uint16_t* buf16[2] = {nullptr, nullptr};
+  uint16_t* xrows = nullptr;
+  int xrow_steps = 0;
   void* H[AGN_MAX_LAYERS + 1] = {};
   void* dZ[AGN_MAX_LAYERS + 1] = {};
   float* Z = nullptr;
@@ -113,6 +118,10 @@ thread_local LaunchEvents g_launch_events{nullptr, nullptr};
 }
 
 namespace {
+
+// aligned copies of a whole round's mini-batches are made by one launch up to
+// this size (256 MiB), step by step beyond
+constexpr int64_t kXrowElements = (int64_t)1 << 27;
 
 inline int64_t round_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
@@ -252,6 +261,12 @@ int enqueue_step(agn_ctx* c, const agn_data* d, int64_t S, int step) {
   const int64_t d0 = c->dims[0];
   const int x_vec = (d0 % (bf ? 8 : 4) == 0) && ((uintptr_t)d->x % 16 == 0);
   Operand xop{d->x, d0, 0, 1, x_vec};
+  if (c->xrows) {
+    if (step % c->xrow_steps == 0)
+      HIP_CHECK(c, launch_gather_rows16((const uint16_t*)d->x, d0, gath, n, std::min(c->xrow_steps, c->lam - step),
+                                        c->xrows, c->lda[0], c->ls));
+    xop = Operand{c->xrows + (int64_t)(step % c->xrow_steps) * n * m * c->lda[0], c->lda[0], (int64_t)m * c->lda[0], 0, 1};
+  }
   auto gemm = [&](int a_kc, int b_kc, const GemmArgs& g) {
     return bf ? launch_gemm_bf16(a_kc, b_kc, g, c->ls) : launch_gemm_f32(a_kc, b_kc, g, c->ls);
   };
@@ -727,6 +742,11 @@ int agn_create(const agn_shapes* shapes, int32_t n, int32_t lambda, float eta, u
   if (ok && bf)
     ok = dalloc(c, &c->snap16, nps) == hipSuccess && dalloc(c, &c->buf16[0], nps) == hipSuccess &&
          dalloc(c, &c->buf16[1], nps) == hipSuccess;
+  if (ok && bf && c->dims[0] % 8 != 0) {
+    const int64_t step = (int64_t)n * c->m * c->lda[0];
+    c->xrow_steps = step * lambda <= kXrowElements ? lambda : 1;
+    ok = dalloc(c, &c->xrows, step * c->xrow_steps) == hipSuccess;
+  }
   for (int l = 1; ok && l <= L; ++l) {
     char* p = nullptr;
     const int64_t bytes = (int64_t)n * c->m * c->lda[l] * act;

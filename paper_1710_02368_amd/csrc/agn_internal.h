@@ -125,6 +125,17 @@ bool gemm_bf16_dl_ok(int a_kc, int b_kc, const GemmArgs& g);
 hipError_t launch_gemm_bf16_dl(int a_kc, int b_kc, const GemmArgs& g, hipStream_t s);
 hipError_t launch_gemm_bf16_dl_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s);
 
+// bf16 products in small tiles (few 128 x 128 tiles, or a K that those do not
+// take), used when gemm_bf16_small_ok
+bool gemm_bf16_small_ok(const GemmArgs& g);
+hipError_t launch_gemm_bf16_small(int a_kc, int b_kc, const GemmArgs& g, hipStream_t s);
+hipError_t launch_gemm_bf16_small_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s);
+// the mini-batches of `steps` local steps (from g.step on) of every worker,
+// gathered into rows of ld elements (a multiple of 8; zeros past d):
+// out[steps][n][m][ld], for data rows that no 16-byte load fits
+hipError_t launch_gather_rows16(const uint16_t* x, int64_t d, const Gather& g, int32_t n, int32_t steps, uint16_t* out,
+                                int64_t ld, hipStream_t s);
+
 struct SoftmaxArgs {
   const float* z;      // logits [n][m][ldz]
   int64_t ldz, zstride;

@@ -192,6 +192,25 @@ __global__ void copy_bf16_kernel(const float* src, uint16_t* dst, int64_t count)
   if (e < count) dst[e] = f32_to_bf16_rne(src[e]);
 }
 
+// one 16-byte chunk of an aligned copy of a mini-batch row per thread
+__global__ __launch_bounds__(256) void gather_rows16_kernel(const uint16_t* x, int64_t d, Gather g, int32_t n,
+                                                            int64_t chunks, uint16_t* out, int64_t ld) {
+  const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (c >= chunks) return;
+  const int64_t per = ld / 8, row = c / per, col = 8 * (c % per);  // row = (step * n + worker) * m + j
+  const int64_t j = row % g.mb, k = row / g.mb % n, step = row / g.mb / n;
+  const uint16_t* src = x + batch_row(k, gather_step(g) + step, g.mb, g.S, j) * d + col;
+  uint32_t e[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) e[i] = col + i < d ? src[i] : 0;
+  uint4 v;
+  v.x = e[0] | (e[1] << 16);
+  v.y = e[2] | (e[3] << 16);
+  v.z = e[4] | (e[5] << 16);
+  v.w = e[6] | (e[7] << 16);
+  *reinterpret_cast<uint4*>(out + row * ld + col) = v;
+}
+
 // Evaluation of one row per wave: loss = logsumexp(z) - z_y and the
 // predicted class argmax z.  Argmax order: a NaN beats any number, a larger
 // value beats a smaller one, and among equals (or among NaNs) the lower
@@ -341,6 +360,13 @@ hipError_t launch_batch_indices(int32_t worker, int64_t t, int32_t mb, int64_t S
                                 hipStream_t s) {
   AGN_LAUNCH(batch_indices_kernel, dim3(blocks_for(mb, 256)), dim3(256), 0, s, worker, t, mb,
                      S, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_gather_rows16(const uint16_t* x, int64_t d, const Gather& g, int32_t n, int32_t steps, uint16_t* out,
+                                int64_t ld, hipStream_t s) {
+  const int64_t chunks = (int64_t)steps * n * g.mb * (ld / 8);
+  AGN_LAUNCH(gather_rows16_kernel, dim3(blocks_for(chunks, 256)), dim3(256), 0, s, x, d, g, n, chunks, out, ld);
   return hipGetLastError();
 }
 

@@ -113,8 +113,8 @@ __device__ __forceinline__ void dw_epilogue_lds(const GemmArgs& g, int worker, i
 // float32 accumulator tile goes to LDS, then each thread takes row chunks of
 // the output (8 bf16 or 4 float32 columns) with their operands (bias, ReLU
 // mask) loaded up front from indices clamped into the matrix, and stores
-// each chunk with one 16-byte store (element by element only where a chunk
-// crosses the matrix edge, so padding columns are never written).
+// each chunk with one 16-byte store (float32 outputs element by element where
+// a chunk crosses the matrix edge; bf16 outputs whole, the row padding as zeros).
 template <int EPI>
 __device__ __forceinline__ void out_epilogue_lds(const GemmArgs& g, int worker, int m0, int n0,
                                                  const f32x16 (&acc)[2][2], float* et) {
@@ -191,27 +191,22 @@ __device__ __forceinline__ void out_epilogue_lds(const GemmArgs& g, int worker, 
 #pragma unroll
         for (int j = 0; j < CW; ++j) {
           const float h = v[j] + bv[j];
-          hv[j] = f32_to_bf16_rne(h > 0.f ? h : 0.f);
+          hv[j] = f32_to_bf16_rne(h > 0.f && cbase + j < g.N ? h : 0.f);  // (the row padding as zeros)
         }
       } else {  // EPI_DX_MASK
         const uint32_t mw[4] = {mv[u].x, mv[u].y, mv[u].z, mv[u].w};
 #pragma unroll
         for (int j = 0; j < CW; ++j) {
           const uint16_t m = (uint16_t)(mw[j / 2] >> (16 * (j % 2)));
-          hv[j] = f32_to_bf16_rne(bf16_to_f32(m) > 0.f ? v[j] : 0.f);
+          hv[j] = f32_to_bf16_rne(bf16_to_f32(m) > 0.f && cbase + j < g.N ? v[j] : 0.f);
         }
       }
-      uint16_t* out = reinterpret_cast<uint16_t*>(g.out) + o;
-      if (whole) {
-        uint4 pk;
-        pk.x = (uint32_t)hv[0] | ((uint32_t)hv[1] << 16);
-        pk.y = (uint32_t)hv[2] | ((uint32_t)hv[3] << 16);
-        pk.z = (uint32_t)hv[4] | ((uint32_t)hv[5] << 16);
-        pk.w = (uint32_t)hv[6] | ((uint32_t)hv[7] << 16);
-        *reinterpret_cast<uint4*>(out) = pk;
-      } else {
-        for (int j = 0; j < CW && cbase + j < g.N; ++j) out[j] = hv[j];
-      }
+      uint4 pk;
+      pk.x = (uint32_t)hv[0] | ((uint32_t)hv[1] << 16);
+      pk.y = (uint32_t)hv[2] | ((uint32_t)hv[3] << 16);
+      pk.z = (uint32_t)hv[4] | ((uint32_t)hv[5] << 16);
+      pk.w = (uint32_t)hv[6] | ((uint32_t)hv[7] << 16);
+      *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(g.out) + o) = pk;
     }
   }
 }

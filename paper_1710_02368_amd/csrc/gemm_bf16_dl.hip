@@ -511,19 +511,14 @@ __device__ __forceinline__ void out_epilogue_big8(const GemmArgs& g, int worker,
 #pragma unroll
         for (int j = 0; j < CW; ++j) {
           const float z = v[j] + bv[j];
-          hv[j] = f32_to_bf16_rne(z > 0.f ? z : 0.f);
+          hv[j] = f32_to_bf16_rne(z > 0.f && cbase + j < g.N ? z : 0.f);  // (the row padding as zeros)
         }
-        uint16_t* out = reinterpret_cast<uint16_t*>(g.out) + o;
-        if (whole) {
-          uint4 pk;
-          pk.x = (uint32_t)hv[0] | ((uint32_t)hv[1] << 16);
-          pk.y = (uint32_t)hv[2] | ((uint32_t)hv[3] << 16);
-          pk.z = (uint32_t)hv[4] | ((uint32_t)hv[5] << 16);
-          pk.w = (uint32_t)hv[6] | ((uint32_t)hv[7] << 16);
-          *reinterpret_cast<uint4*>(out) = pk;
-        } else {
-          for (int j = 0; j < CW && cbase + j < g.N; ++j) out[j] = hv[j];
-        }
+        uint4 pk;
+        pk.x = (uint32_t)hv[0] | ((uint32_t)hv[1] << 16);
+        pk.y = (uint32_t)hv[2] | ((uint32_t)hv[3] << 16);
+        pk.z = (uint32_t)hv[4] | ((uint32_t)hv[5] << 16);
+        pk.w = (uint32_t)hv[6] | ((uint32_t)hv[7] << 16);
+        *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(g.out) + o) = pk;
       }
     }
   }

@@ -37,6 +37,7 @@ typedef float sp_f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 sp_bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 sp_bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t sp_u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t sp_u32x2 __attribute__((ext_vector_type(2)));
 
 // eight float32 values -> their three bf16 pieces, 16 bytes each
 __device__ __forceinline__ void split8(const float (&x)[8], sp_u32x4& h, sp_u32x4& m, sp_u32x4& l) {
@@ -138,8 +139,9 @@ struct SplitCoord {
 // Operands of the epilogue, loaded from indices clamped into the matrix (its
 // rows are padded to 8; values outside are never stored): the bias, the ReLU
 // mask, or the weights (with the snapshot on a round's last step, and Adam's
-// moments).
-template <class Cfg, int EPI, bool ADAM>
+// moments).  H16: activations and gradients are bf16, and the updated weights'
+// bf16 shadow is written beside them.
+template <class Cfg, int EPI, bool ADAM, bool H16 = false>
 struct SplitEpilogue {
   static constexpr int NC = Cfg::NC;
   static constexpr bool DW = EPI == EPI_DW_UPDATE;
@@ -152,8 +154,14 @@ struct SplitEpilogue {
       for (int i = 0; i < NC; ++i) {
         const int64_t row = min(c.m0 + c.er0 + i * c.ERS, g.M - 1);
         if (EPI == EPI_DX_MASK) {
-          pre[i] = *reinterpret_cast<const sp_f32x4*>(reinterpret_cast<const float*>(g.mask) + c.worker * g.mstride +
-                                                      row * g.ldm + cc);
+          const int64_t e = c.worker * g.mstride + row * g.ldm + cc;
+          if (H16) {
+            const sp_u32x2 t = *reinterpret_cast<const sp_u32x2*>(reinterpret_cast<const uint16_t*>(g.mask) + e);
+            pre[i] = sp_f32x4{__uint_as_float(t[0] << 16), __uint_as_float(t[0] & 0xFFFF0000u),
+                              __uint_as_float(t[1] << 16), __uint_as_float(t[1] & 0xFFFF0000u)};
+          } else {
+            pre[i] = *reinterpret_cast<const sp_f32x4*>(reinterpret_cast<const float*>(g.mask) + e);
+          }
         } else {
           const int64_t e = c.worker * g.pstride + row * g.ldw + cc;
           pre[i] = *reinterpret_cast<const sp_f32x4*>(g.w_src + e);
@@ -171,12 +179,17 @@ struct SplitEpilogue {
     }
   }
 
+  static __device__ __forceinline__ sp_u32x2 bf16_of(const sp_f32x4& v) {
+    return sp_u32x2{(uint32_t)f32_to_bf16_rne(v[0]) | ((uint32_t)f32_to_bf16_rne(v[1]) << 16),
+                    (uint32_t)f32_to_bf16_rne(v[2]) | ((uint32_t)f32_to_bf16_rne(v[3]) << 16)};
+  }
+
   // v: this thread's chunks of the product; gb: the bias gradient of row tid
   // (first column tile of a weight gradient)
   __device__ __forceinline__ void store(const GemmArgs& g, const SplitCoord<Cfg>& c, const sp_f32x4 (&v)[NC], float gb) {
     if (!DW) {
       if (c.mine && c.ec < g.ldo) {  // (columns past N are stored as zeros: the row padding stays zero)
-        float* out = reinterpret_cast<float*>(g.out) + c.worker * g.ostride + c.ec;
+        const int64_t e0 = c.worker * g.ostride + c.ec;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
           const int64_t row = c.m0 + c.er0 + i * c.ERS;
@@ -193,7 +206,10 @@ struct SplitEpilogue {
             }
             o[e] = c.ec + e < g.N ? x : 0.f;
           }
-          *reinterpret_cast<sp_f32x4*>(out + row * g.ldo) = o;
+          if (H16 && EPI != EPI_FWD_LINEAR)
+            *reinterpret_cast<sp_u32x2*>(reinterpret_cast<uint16_t*>(g.out) + e0 + row * g.ldo) = bf16_of(o);
+          else
+            *reinterpret_cast<sp_f32x4*>(reinterpret_cast<float*>(g.out) + e0 + row * g.ldo) = o;
         }
       }
       return;
@@ -221,6 +237,7 @@ struct SplitEpilogue {
         }
         if (c.ec + 4 <= g.N) {
           *reinterpret_cast<sp_f32x4*>(g.w_dst + e0) = o;
+          if (H16 && !g.last) *reinterpret_cast<sp_u32x2*>(g.w_dst16 + e0) = bf16_of(o);
           if (ADAM) {
             *reinterpret_cast<sp_f32x4*>(g.adam.mw + e0) = mo[i];
             *reinterpret_cast<sp_f32x4*>(g.adam.vw + e0) = ve[i];
@@ -228,6 +245,7 @@ struct SplitEpilogue {
         } else {
           for (int e = 0; e < 4 && c.ec + e < g.N; ++e) {
             g.w_dst[e0 + e] = o[e];
+            if (H16 && !g.last) g.w_dst16[e0 + e] = f32_to_bf16_rne(o[e]);
             if (ADAM) g.adam.mw[e0 + e] = mo[i][e], g.adam.vw[e0 + e] = ve[i][e];
           }
         }
@@ -243,10 +261,10 @@ struct SplitEpilogue {
 };
 
 // The waves' accumulators to LDS and each thread's chunks back in row order,
-// the KW partial sums added in wave order.  A result that is not finite makes
-// the workgroup compute its tile again with float32 MFMAs straight from
+// the KW partial sums added in wave order.  RETRY: a result that is not finite
+// makes the workgroup compute its tile again with float32 MFMAs straight from
 // memory.  lds is free when this is called (a barrier lies before).
-template <class Cfg, class Place, bool A_KC, bool B_KC>
+template <class Cfg, class Place, bool A_KC, bool B_KC, bool RETRY = true>
 __device__ __forceinline__ void split_gather(const GemmArgs& g, const SplitCoord<Cfg>& c, float* et,
                                              sp_f32x16 (&acc)[Cfg::WTM / 32][Cfg::WTN / 32], sp_f32x4 (&v)[Cfg::NC]) {
   constexpr int MB = Cfg::WTM / 32, NB = Cfg::WTN / 32, NC = Cfg::NC, KW = Cfg::KW, BM = Cfg::BM, ELD = Cfg::ELD;
@@ -270,7 +288,7 @@ __device__ __forceinline__ void split_gather(const GemmArgs& g, const SplitCoord
 #pragma unroll
       for (int e = 0; e < 4; ++e) chk += v[i][e] * 0.f;
     }
-    if (pass || !__syncthreads_or(chk != 0.f)) return;
+    if (!RETRY || pass || !__syncthreads_or(chk != 0.f)) return;
     const int64_t t = g.a.gather || g.b.gather ? gather_step(g.g) : 0;
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)

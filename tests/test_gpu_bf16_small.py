@@ -1,0 +1,52 @@
+"""The small-tile bf16 products at the edges of their tiles, against the
+oracle: K that is no multiple of 8 or of a step, ragged rows and columns,
+data rows that no 16-byte load fits (copied into aligned rows for a whole
+round, or step by step where that is large), batches that wrap round their
+shard or exceed it."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import AGNOracle
+from tests.helpers import rel_err, to_device
+
+pytestmark = pytest.mark.gpu
+
+# dims, n, lambda, m, N
+CASES = {
+    "one_wave": ((104, 37, 70, 12), 2, 2, 20, 400),            # 32 x 32 tiles, forward K = 37
+    "k_below_a_step": ((8, 33, 5, 3), 3, 3, 7, 100),
+    "unaligned": ((101, 71, 60, 40), 2, 3, 20, 400),
+    "quad": ((72, 517, 259, 37), 16, 2, 77, 16 * 100),         # 64 x 64 tiles, wraps round the shard
+    "unaligned_quad": ((123, 517, 259, 37), 16, 2, 77, 16 * 100),
+    "batch_over_shard": ((48, 70, 66, 10), 2, 2, 50, 60),      # m = 50 rows of shards of 30
+    "rows_step_by_step": ((3071, 16, 5), 2, 90, 256, 600),     # a round's rows exceed the copy's bound
+}
+BF16_TOL = 2e-2  # the stated bound of bf16 central variables
+
+
+@pytest.mark.parametrize("case", CASES)
+@pytest.mark.parametrize("adam", [None, (0.9, 0.999, 1e-5)], ids=["sgd", "adam"])
+def test_bf16_round_matches_oracle(case, adam):
+    import paper_1710_02368_amd as agn
+    dims, n, lam, m, N = CASES[case]
+    print(case, dims, n, lam, m, N, adam, flush=True)
+    wl = W.small_workload(case, dims, n, lam, m, 0.02 if adam is None else 0.001, 1, N, order="permutation",
+                          dtype="bf16")
+    X, y = W.make_data(wl)
+    xd, yd = to_device(X, y)
+    g = agn.AGN(dims, n, lam, wl.eta, m, seed=3, dtype="bf16", adam=adam)
+    o = AGNOracle(dims, n, lam, wl.eta, m, seed=3, bf16=True, adam=adam)
+    order = W.commit_orders(wl)[0]
+    g.round(xd, yd, order)
+    o.round(X, y, order)
+    # bf16 activations: an operand one step of 2^-8 off moves a loss by less
+    np.testing.assert_allclose(g.loss().cpu().numpy(), o.last_loss, rtol=5e-3)
+    got, ref = g.central().cpu().numpy(), o.central_flat()
+    err, where = rel_err(got, ref, dims) if adam is None else (0.0, None)
+    assert err <= BF16_TOL, (where, err)
+    assert np.linalg.norm(got - ref.astype(np.float64)) <= BF16_TOL * np.linalg.norm(ref)
+    # the round's total step in the 2-norm: bf16 deltas differ by up to 9e-2
+    init = o.__class__(dims, n, lam, wl.eta, m, seed=3, bf16=True).central_flat().astype(np.float64)
+    assert np.linalg.norm(got - ref.astype(np.float64)) <= 0.1 * np.linalg.norm(ref - init)
+    g.close()

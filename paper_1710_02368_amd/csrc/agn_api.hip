@@ -94,7 +94,7 @@ struct agn_ctx {
   // evaluation workspace (allocated by the first agn_evaluate call)
   void* ev_h[2] = {nullptr, nullptr};  // activations of EVAL_CHUNK rows, ping-pong
   float* ev_z = nullptr;               // logits of EVAL_CHUNK rows (unfused output layer)
-  uint16_t* ev_w16 = nullptr;          // bf16 copy of the central variable
+  uint16_t* ev_x = nullptr;            // aligned copies of EVAL_CHUNK data rows (bf16, rows that no 16-byte load fits)
   double* ev_part = nullptr;           // per-block partial sums of one chunk
   double* ev_acc = nullptr;            // loss sum and correct count over all rows
   int64_t eval_N = 0;                  // rows of the last agn_evaluate call
@@ -472,25 +472,38 @@ int enqueue_round(agn_ctx* c, const agn_data* d) {
 
 // Rows the evaluation takes through its forward pass at a time: large
 // enough that each product of a 1000-wide layer spreads over several
-// workgroups per compute unit.
+// workgroups per compute unit.  In float32 twice as many, where that keeps
+// the activations under 1 GiB, so that 10,000 rows are one pass (784-1000-
+// 1000-10: 300 us against 352 in two); in bf16 8192 rows of a
+// 2048-wide layer are one round of 256 x 256 tiles (10,000 would take two).
 constexpr int64_t EVAL_CHUNK = 8192;
+
+// widest row of a hidden layer's activations
+int64_t eval_width(const agn_ctx* c) {
+  int64_t wmax = 0;
+  for (int l = 1; l < c->L; ++l) wmax = std::max(wmax, c->lda[l]);
+  return wmax;
+}
+
+int64_t eval_chunk(const agn_ctx* c) {
+  return c->dtype == AGN_FP32 && 2 * EVAL_CHUNK * eval_width(c) * 2 * 4 <= ((int64_t)1 << 30) ? 2 * EVAL_CHUNK : EVAL_CHUNK;
+}
 
 // The evaluation's own buffers (nothing a round uses), allocated once.
 int eval_alloc(agn_ctx* c) {
   if (c->ev_acc) return AGN_OK;
   const bool bf = c->dtype == AGN_BF16;
-  int64_t wmax = 0;
-  for (int l = 1; l < c->L; ++l) wmax = std::max(wmax, c->lda[l]);
+  const int64_t wmax = eval_width(c), chunk = eval_chunk(c);
   const int64_t act = bf ? 2 : 4;
-  const int64_t blocks = std::max(eval_blocks(EVAL_CHUNK), head_eval_blocks(EVAL_CHUNK));
+  const int64_t blocks = std::max(eval_blocks(chunk), head_eval_blocks(chunk));
   // (a failed call keeps what it got; the next call allocates the rest)
   bool ok = true;
   for (int i = 0; ok && i < 2 && wmax > 0; ++i) {
     char* p = nullptr;
-    if (!c->ev_h[i]) ok = dalloc(c, &p, EVAL_CHUNK * wmax * act) == hipSuccess, c->ev_h[i] = p;
+    if (!c->ev_h[i]) ok = dalloc(c, &p, chunk * wmax * act) == hipSuccess, c->ev_h[i] = p;
   }
-  if (ok && !c->use_head && !c->ev_z) ok = dalloc(c, &c->ev_z, EVAL_CHUNK * c->lda[c->L]) == hipSuccess;
-  if (ok && bf && !c->ev_w16) ok = dalloc(c, &c->ev_w16, c->P_pad) == hipSuccess;
+  if (ok && !c->use_head && !c->ev_z) ok = dalloc(c, &c->ev_z, chunk * c->lda[c->L]) == hipSuccess;
+  if (ok && c->xrows && !c->ev_x) ok = dalloc(c, &c->ev_x, chunk * c->lda[0]) == hipSuccess;
   if (ok && !c->ev_part) ok = dalloc(c, &c->ev_part, 2 * blocks) == hipSuccess;
   double* acc = nullptr;
   if (ok) ok = dalloc(c, &acc, 2) == hipSuccess;
@@ -500,13 +513,13 @@ int eval_alloc(agn_ctx* c) {
 }
 
 // Buffers of one evaluation: activations of `chunk` rows (ping-pong, the
-// widest hidden layer), their logits (unfused output layer), the bf16
-// operands of the central variable (bf16 contexts), per-block partial sums
-// of one chunk and the float64 totals.
+// widest hidden layer), their logits (unfused output layer), aligned copies
+// of the data rows (agn_evaluate, where no 16-byte load fits them), per-block
+// partial sums of one chunk and the float64 totals.
 struct EvalSpace {
   void* h[2];
   float* z;
-  const uint16_t* w16;
+  uint16_t* x;  // (null: the data rows are read where they lie)
   double* part;
   double* acc;
   int64_t chunk;
@@ -516,8 +529,7 @@ struct EvalSpace {
 // the buffers when base != nullptr.
 int64_t eval_space_bytes(const agn_ctx* c, int64_t rows, unsigned char* base, EvalSpace* ws) {
   const bool bf = c->dtype == AGN_BF16;
-  int64_t wmax = 0;
-  for (int l = 1; l < c->L; ++l) wmax = std::max(wmax, c->lda[l]);
+  const int64_t wmax = eval_width(c);
   const int64_t act = bf ? 2 : 4;
   const int64_t blocks = std::max(eval_blocks(rows), head_eval_blocks(rows));
   int64_t off = 0;
@@ -538,7 +550,7 @@ int64_t eval_space_bytes(const agn_ctx* c, int64_t rows, unsigned char* base, Ev
     ws->part = reinterpret_cast<double*>(part);
     ws->acc = reinterpret_cast<double*>(acc);
     ws->chunk = rows;
-    ws->w16 = nullptr;
+    ws->x = nullptr;
   }
   return off;
 }
@@ -555,18 +567,28 @@ int enqueue_eval(agn_ctx* c, const agn_data* d, float* row_loss, int32_t* row_pr
   const int64_t xes = bf ? 2 : 4;
   const Gather rows_as_stored{c->round_dev, c->lam, 0, c->m, 1};  // (no gathered operand)
   const int products = c->use_head ? L - 1 : L;
+  // bf16 operands of the central variable: the copy that the last commit
+  // wrote for the last committer's pull (before the first round, and after
+  // agn_set_central, every worker's copy is the central one)
+  const uint16_t* w16 = bf ? c->snap16 + (int64_t)c->last_committer * c->P_pad : nullptr;
   for (int64_t r0 = 0; r0 < N; r0 += ws.chunk) {
     const int32_t rows = (int32_t)std::min(ws.chunk, N - r0);
     const void* x = static_cast<const char*>(d->x) + r0 * d0 * xes;
     const int x_vec = (d0 % (bf ? 8 : 4) == 0) && ((uintptr_t)x % 16 == 0);
+    Operand xop{x, d0, 0, 0, x_vec};
+    if (ws.x) {  // (one batch of these rows at step 0 of round 0)
+      const Gather as_one{reinterpret_cast<const int64_t*>(c->zero), 1, 0, rows, rows};
+      HIP_CHECK(c, launch_gather_rows16(static_cast<const uint16_t*>(x), d0, as_one, 1, 1, ws.x, c->lda[0], c->ls));
+      xop = Operand{ws.x, c->lda[0], 0, 0, 1};
+    }
     for (int l = 0; l < products; ++l) {
       GemmArgs g{};
       g.M = rows;
       g.N = c->dims[l + 1];
       g.K = c->dims[l];
       g.batch = 1;
-      g.a = l == 0 ? Operand{x, d0, 0, 0, x_vec} : Operand{ws.h[(l - 1) & 1], c->lda[l], 0, 0, 1};
-      g.b = bf ? Operand{ws.w16 + c->woff[l], c->ldw[l], 0, 0, 1}
+      g.a = l == 0 ? xop : Operand{ws.h[(l - 1) & 1], c->lda[l], 0, 0, 1};
+      g.b = bf ? Operand{w16 + c->woff[l], c->ldw[l], 0, 0, 1}
                : Operand{c->central + c->woff[l], c->ldw[l], 0, 0, 1};
       g.g = rows_as_stored;
       g.epi = l < L - 1 ? EPI_FWD_RELU : EPI_FWD_LINEAR;
@@ -947,8 +969,7 @@ int agn_evaluate(agn_ctx* c, const agn_data* d, float* row_loss, int32_t* row_pr
   if (int r = set_device(c)) return r;
   if (int r = eval_alloc(c)) return r;
   c->ls = c->stream;
-  const EvalSpace ws{{c->ev_h[0], c->ev_h[1]}, c->ev_z, c->ev_w16, c->ev_part, c->ev_acc, EVAL_CHUNK};
-  if (c->dtype == AGN_BF16) HIP_CHECK(c, launch_copy_bf16(c->central, c->ev_w16, c->P_pad, c->ls));
+  const EvalSpace ws{{c->ev_h[0], c->ev_h[1]}, c->ev_z, c->ev_x, c->ev_part, c->ev_acc, eval_chunk(c)};
   if (int r = enqueue_eval(c, d, row_loss, row_pred, ws)) return r;
   c->eval_N = d->num_samples;
   return eval_result(c, ws, d->num_samples, out);
@@ -973,10 +994,6 @@ int agn_evaluate_noalloc(agn_ctx* c, const agn_data* d, float* row_loss, int32_t
   if (int r = set_device(c)) return r;
   EvalSpace ws{};
   eval_space_bytes(c, rows, c->scratch, &ws);
-  // bf16 operands of the central variable: the bf16 copy that the last
-  // commit wrote for the last committer's pull (before the first round,
-  // and after agn_set_central, every worker's copy is the central one)
-  if (c->dtype == AGN_BF16) ws.w16 = c->snap16 + (int64_t)c->last_committer * c->P_pad;
   c->ls = c->stream;
   c->untimed = 1;
   const int r = enqueue_eval(c, d, row_loss, row_pred, ws);

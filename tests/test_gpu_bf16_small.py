@@ -50,3 +50,30 @@ def test_bf16_round_matches_oracle(case, adam):
     init = o.__class__(dims, n, lam, wl.eta, m, seed=3, bf16=True).central_flat().astype(np.float64)
     assert np.linalg.norm(got - ref.astype(np.float64)) <= 0.1 * np.linalg.norm(ref - init)
     g.close()
+
+
+def test_bf16_evaluation_of_unaligned_rows_matches_the_direct_path():
+    """agn_evaluate copies rows that no 16-byte load fits, agn_evaluate_noalloc
+    reads them where they lie: the same sums in the same order, bit for bit,
+    over two passes of rows, before and after a round."""
+    import torch
+
+    import paper_1710_02368_amd as agn
+    from paper_1710_02368_amd import agn as binding
+    dims, n, rows = (101, 71, 60, 40), 2, 9000
+    wl = W.small_workload("eval16", dims, n, 2, 20, 0.05, 1, rows, dtype="bf16")
+    X, y = W.make_data(wl)
+    xd, yd = to_device(X, y)
+    g = agn.AGN(dims, n, 2, 0.05, 20, seed=3, dtype="bf16")
+    for _ in range(2):
+        out = []
+        for fn in (binding.agn_evaluate, binding.agn_evaluate_noalloc):
+            rl = torch.full((rows,), float("nan"), dtype=torch.float32, device="cuda")
+            rp = torch.full((rows,), -1, dtype=torch.int32, device="cuda")
+            res = fn(g.ctx, xd, yd, rows, agn.AGN_BF16, rl, rp)
+            out.append((res, rl.cpu().numpy(), rp.cpu().numpy()))
+        np.testing.assert_array_equal(out[0][1].view(np.int32), out[1][1].view(np.int32))
+        np.testing.assert_array_equal(out[0][2], out[1][2])
+        assert out[0][0][2] == out[1][0][2]
+        g.round(xd, yd, [1, 0])
+    g.close()

@@ -330,8 +330,10 @@ MFMA_FILE = os.path.join(ROOT, "profiles", "mfma_{}.json")
 
 
 def summarize_mfma(d, workload, dtype):
-    """MFMA counter pass (rocprofv3 --pmc MfmaUtil MfmaFlopsF32 (or BF16)
-    GRBM_GUI_ACTIVE, csv output under d/) -> per kernel class: the MFMA busy
+    """MFMA counter pass (rocprofv3 --pmc MfmaUtil MfmaFlopsF32 MfmaFlopsBF16
+    GRBM_GUI_ACTIVE for float32 workloads, without MfmaFlopsF32 for bf16 ones,
+    csv output under d/; a float32 product done as six bf16 products counts
+    as a sixth of its bf16 flops) -> per kernel class: the MFMA busy
     fraction (MfmaUtil: busy cycles of the matrix units over the dispatch's
     active cycles times the SIMD count, averaged over the class's launches
     weighted by their durations) and the MFMA flops the counters saw per
@@ -339,7 +341,8 @@ def summarize_mfma(d, workload, dtype):
     kernel sources, and printed as a text summary."""
     import collections
     import csv
-    flops_name = "MfmaFlopsBF16" if dtype == "bf16" else "MfmaFlopsF32"
+    weights = {"MfmaFlopsBF16": 1.0} if dtype == "bf16" else {"MfmaFlopsF32": 1.0, "MfmaFlopsBF16": 1.0 / 6}
+    flops_name = "MfmaFlopsBF16" if dtype == "bf16" else "MfmaFlopsF32 + MfmaFlopsBF16 / 6"
     per = collections.defaultdict(dict)
     names, dur = {}, {}
     with open(os.path.join(d, "run_counter_collection.csv")) as fh:
@@ -359,7 +362,7 @@ def summarize_mfma(d, workload, dtype):
             e = table[key]
             e["busy_w"] += v["MfmaUtil"] / 100.0 * dur[k]
             e["active"] += dur[k]
-            e["flops"] += v.get(flops_name, 0.0)
+            e["flops"] += sum(w * v.get(name, 0.0) for name, w in weights.items())
             e["launches"] += 1
     out = {"workload": workload, "kernel_source_sha256": kernel_source_digest(), "counter_flops": flops_name,
            "classes": {}}

@@ -180,10 +180,12 @@ typedef struct {
  *   row_pred: DEVICE, num_samples int32, or NULL.
  *   out:      HOST, or NULL.  The mean loss is summed in float64 in a
  *             fixed order: repeated calls give identical results.
- * Rows go through the forward pass 8192 at a time in the evaluation's own
- * workspace, which the first call allocates (activations of 8192 rows, two
- * buffers of the widest hidden layer; AGN_ENOMEM if that fails) and no
- * round touches: a call between rounds changes nothing a round reads.  It
+ * Rows go through the forward pass 8192 at a time (float32: 16384 while the
+ * activations stay under 1 GiB) in the evaluation's own workspace, which the
+ * first call that needs a part of it allocates (activations of that many
+ * rows, two buffers of the widest hidden layer; in AGN_BF16 contexts an
+ * aligned copy of data rows that no 16-byte load fits; AGN_ENOMEM if that
+ * fails) and no round touches: a call between rounds changes nothing a round reads.  It
  * works before the first round (the initial model).  With out != NULL the
  * call waits for the stream; with out == NULL it returns after enqueueing. */
 int agn_evaluate(agn_ctx* ctx, const agn_data* data, float* row_loss, int32_t* row_pred,

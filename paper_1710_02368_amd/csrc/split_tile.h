@@ -1,9 +1,10 @@
 // Float32 products on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), each
 // float32 operand split into three bf16 pieces x = h + m + l.
 //
-// The split is exact for normal float32 values: h = bf16(x), m = bf16(x - h),
-// l = x - h - m hold 8 bits each, rounded to nearest, and the subtractions
-// are exact.  A product a*b is the sum of the six piece products
+// The split is exact for float32 values of at least 2^-102: h = bf16(x),
+// m = bf16(x - h), l = x - h - m hold 8 bits each, rounded to nearest, and the
+// subtractions are exact.  (The matrix cores read subnormal pieces as zero:
+// a smaller value may lose up to 2^-126.)  A product a*b is the sum of the six piece products
 // ah*bh + (ah*bm + am*bh) + (am*bm + ah*bl + al*bh); the three left out are
 // below 2^-26 of it.  ah*bh goes to one accumulator, the five small ones to
 // a second, added at the end: one rounding per 16 k in the large sum, where

@@ -1,10 +1,14 @@
 // Float32 products on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), each
 // float32 operand split into three bf16 pieces x = h + m + l.
 //
-// The split is exact for float32 values of at least 2^-102: h = bf16(x),
-// m = bf16(x - h), l = x - h - m hold 8 bits each, rounded to nearest, and the
-// subtractions are exact.  (The matrix cores read subnormal pieces as zero:
-// a smaller value may lose up to 2^-126.)  A product a*b is the sum of the six piece products
+// The split is exact: h = bf16(x), m = bf16(x - h), l = x - h - m hold 8 bits
+// each, rounded to nearest, and the subtractions are exact.  Every operand is
+// split as 2^16 x: a float32 value is a multiple of 2^-149 and a bf16 one of
+// 2^-133, which without the factor would take the low bits of values below
+// 2^-110, 16 of the 24 at 2^-126.  (Conversion, dot product and MFMA keep
+// subnormal values.)  The sums come out 2^32 too large and are scaled back
+// before anything else is done with them; in range the factors change no bit.
+// A product a*b is the sum of the six piece products
 // ah*bh + (ah*bm + am*bh) + (am*bm + ah*bl + al*bh); the three left out are
 // below 2^-26 of it.  ah*bh goes to one accumulator, the five small ones to
 // a second, added at the end: one rounding per 16 k in the large sum, where
@@ -15,16 +19,20 @@
 // MFMAs' cycles at the nominal rates; with random operands the card sustains
 // 1.75 PFLOP/s in bf16 (292 TFLOP/s of split products) against 154 in float32.
 //
-// The split takes 3.5 vector instructions per element: v_cvt_pk_bf16_f32
-// rounds two elements to a packed pair, v_dot2c_f32_bf16 subtracts one piece
-// of that pair from its element (dot with (-1, 0) or (0, -1)).  Masks and
-// subtractions (5.5 per element) overlap with MFMAs, which the dot products
-// do not, and still measured slower (forward product 40 x 128 x 2000 x 2000:
-// 271 against 256 us; weight gradient 547 against 518).
+// The split takes 4.5 vector instructions per element: the factor,
+// v_cvt_pk_bf16_f32, which rounds two elements to a packed pair, and
+// v_dot2c_f32_bf16, which subtracts one piece of that pair from its element
+// (dot with (-1, 0) or (0, -1)).  Masks and subtractions instead of the dot
+// products (5.5 per element without the factor) overlap with MFMAs, which
+// those do not, and still measured slower (forward product 40 x 128 x 2000 x
+// 2000: 271 against 256 us; weight gradient 547 against 518).  The factor
+// costs a round of 8 x 784-1000-1000-10, m = 128 1897 against 1849 us, of 20
+// workers 4098 against 3974, of 10 x 784-512-256-10, m = 64 573 against 553.
 //
 // Infinities: inf - inf in the split makes NaN where the float32 product
-// would keep an infinity, so a tile with a non-finite result is computed
-// again with float32 MFMAs straight from memory (split_gather).
+// would keep an infinity, and results of 2^96 and more (operands of 2^111)
+// leave the range that the factors leave, so a tile with a non-finite result
+// is computed again with float32 MFMAs straight from memory (split_gather).
 #pragma once
 
 #include "device_common.h"
@@ -40,17 +48,21 @@ typedef __bf16 sp_bf16x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t sp_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t sp_u32x2 __attribute__((ext_vector_type(2)));
 
-// eight float32 values -> their three bf16 pieces, 16 bytes each
+constexpr float kSplitScale = 0x1p16f, kSplitUnscale = 0x1p-32f;  // of an operand; of a product of two
+
+// eight float32 values -> the three bf16 pieces of 2^23 times each, 16 bytes each
 __device__ __forceinline__ void split8(const float (&x)[8], sp_u32x4& h, sp_u32x4& m, sp_u32x4& l) {
   // (-1, 0) and (0, -1), the first from a register: the compiler would encode
   // it as the inline constant -1.0, which the instruction reads as (0, -1)
   uint32_t u0 = 0x0000BF80u;
   asm("" : "+s"(u0));
+  float scale = kSplitScale;  // (from a register too: a literal makes every multiplication eight bytes)
+  asm("" : "+s"(scale));
   const sp_bf16x2 n0 = __builtin_bit_cast(sp_bf16x2, u0);
   const sp_bf16x2 n1 = __builtin_bit_cast(sp_bf16x2, 0xBF800000u);
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
-    const float x0 = x[2 * p], x1 = x[2 * p + 1];
+    const float x0 = x[2 * p] * scale, x1 = x[2 * p + 1] * scale;
     sp_bf16x2 a, b, c;
     a[0] = (__bf16)x0;
     a[1] = (__bf16)x1;
@@ -262,10 +274,11 @@ struct SplitEpilogue {
 };
 
 // The waves' accumulators to LDS and each thread's chunks back in row order,
-// the KW partial sums added in wave order.  RETRY: a result that is not finite
-// makes the workgroup compute its tile again with float32 MFMAs straight from
-// memory.  lds is free when this is called (a barrier lies before).
-template <class Cfg, class Place, bool A_KC, bool B_KC, bool RETRY = true>
+// the KW partial sums added in wave order.  SPLIT: the sums are those of split
+// operands and are scaled back, and a result that is not finite makes the
+// workgroup compute its tile again with float32 MFMAs straight from memory.
+// lds is free when this is called (a barrier lies before).
+template <class Cfg, class Place, bool A_KC, bool B_KC, bool SPLIT = true>
 __device__ __forceinline__ void split_gather(const GemmArgs& g, const SplitCoord<Cfg>& c, float* et,
                                              sp_f32x16 (&acc)[Cfg::WTM / 32][Cfg::WTN / 32], sp_f32x4 (&v)[Cfg::NC]) {
   constexpr int MB = Cfg::WTM / 32, NB = Cfg::WTN / 32, NC = Cfg::NC, KW = Cfg::KW, BM = Cfg::BM, ELD = Cfg::ELD;
@@ -289,7 +302,10 @@ __device__ __forceinline__ void split_gather(const GemmArgs& g, const SplitCoord
 #pragma unroll
       for (int e = 0; e < 4; ++e) chk += v[i][e] * 0.f;
     }
-    if (!RETRY || pass || !__syncthreads_or(chk != 0.f)) return;
+    if (!SPLIT || pass) return;
+#pragma unroll
+    for (int i = 0; i < NC; ++i) v[i] *= kSplitUnscale;
+    if (!__syncthreads_or(chk != 0.f)) return;
     const int64_t t = g.a.gather || g.b.gather ? gather_step(g.g) : 0;
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)

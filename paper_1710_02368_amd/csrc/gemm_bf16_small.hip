@@ -219,7 +219,7 @@ __device__ __forceinline__ void small16_tile(const GemmArgs& g, const int logica
     }
   }
   sp_f32x4 v[Cfg::NC];
-  split_gather<Cfg, SplitPlace<Cfg, false, false>, A_KC, B_KC, false>(g, c, et, acc, v);
+  split_gather<Cfg, SplitPlace<Cfg, false, false>>(c, et, acc, v);
   epi.store(g, c, v, gb);
 }
 

@@ -15,6 +15,8 @@
 //     NB covers columns NB*j + b), a wave's 32 lanes 128 or 256 contiguous bytes.
 #pragma once
 
+#include <type_traits>
+
 #include "direct_load.h"
 #include "split_tile.h"
 
@@ -241,79 +243,98 @@ __device__ __forceinline__ void direct_tile(const GemmArgs& g, const int logical
   const auto fire_b = [&](int t, int stage) { lb.fire(t * BK, lds0 + B0 + stage * OpB::BYTES); };
   SplitEpilogue<Cfg, EPI, ADAM> epi;
   if (EARLY) epi.load(g, c);
-#pragma unroll
-  for (int t = 0; t < NSB - NSA; ++t)
-    if (t < nk) fire_b(t, t);
-#pragma unroll
-  for (int t = 0; t < NSA - 1; ++t) {
-    if (t < nk) fire_a(t, t);
-    if (t + NSB - NSA < nk) fire_b(t + NSB - NSA, t + NSB - NSA);
-  }
 
-  sp_f32x16 acc[MB][NB], low[MB][NB];
-#pragma unroll
-  for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < NB; ++bj)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[bi][bj][r] = low[bi][bj][r] = 0.f;
   // bias gradient (first column tile of a weight gradient): sums of dZ over
   // this lane's k
   const bool do_bias = DW && c.n0 == 0;
   float bsum[MB];
 #pragma unroll
   for (int b = 0; b < MB; ++b) bsum[b] = 0.f;
-  int sa = 0, sb = 0, na = NSA - 1, nb = NSB - 1;  // stages of the next step to read and to load
 
-  // Step t has landed: this wave's loads of it, then every wave's; and every
-  // wave is done reading the stages the next loads overwrite.  Turn u issues
-  // A(u + NSA - 1), then B(u + NSB - 1); step t's last load is followed by
-  // NSA - 2 whole turns, and by its own turn's B where that is a later step's
-  // (NSB > NSA).  At the end of K fewer follow, and all are waited for.
-  const auto arrive = [&](int t) {
-    constexpr int YOUNGER = (NSA - 2) * (OpA::LPS + OpB::LPS) + (NSB > NSA ? OpB::LPS : 0);
-    if (YOUNGER < 64 && t + NSB - 2 < nk)
-      wait_vm<YOUNGER < 64 ? YOUNGER : 0>();
-    else
-      wait_vm<0>();
+  // The products of all K steps, from split operands or (F32: the second pass
+  // of a tile) from the float32 values.
+  sp_f32x16 acc[MB][NB];
+  const auto sweep = [&](auto f32) {
+    constexpr bool F32 = decltype(f32)::value;
+#pragma unroll
+    for (int t = 0; t < NSB - NSA; ++t)
+      if (t < nk) fire_b(t, t);
+#pragma unroll
+    for (int t = 0; t < NSA - 1; ++t) {
+      if (t < nk) fire_a(t, t);
+      if (t + NSB - NSA < nk) fire_b(t + NSB - NSA, t + NSB - NSA);
+    }
+    sp_f32x16 low[MB][NB];
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < NB; ++bj)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[bi][bj][r] = low[bi][bj][r] = 0.f;
+    int sa = 0, sb = 0, na = NSA - 1, nb = NSB - 1;  // stages of the next step to read and to load
+
+    // Step t has landed: this wave's loads of it, then every wave's; and every
+    // wave is done reading the stages the next loads overwrite.  Turn u issues
+    // A(u + NSA - 1), then B(u + NSB - 1); step t's last load is followed by
+    // NSA - 2 whole turns, and by its own turn's B where that is a later step's
+    // (NSB > NSA).  At the end of K fewer follow, and all are waited for.
+    const auto arrive = [&](int t) {
+      constexpr int YOUNGER = (NSA - 2) * (OpA::LPS + OpB::LPS) + (NSB > NSA ? OpB::LPS : 0);
+      if (YOUNGER < 64 && t + NSB - 2 < nk)
+        wait_vm<YOUNGER < 64 ? YOUNGER : 0>();
+      else
+        wait_vm<0>();
+      wait_lgkm0();
+      barrier();
+      if (t + NSA - 1 < nk) fire_a(t + NSA - 1, na);
+      if (t + NSB - 1 < nk) fire_b(t + NSB - 1, nb);
+      na = na + 1 == NSA ? 0 : na + 1;
+      nb = nb + 1 == NSB ? 0 : nb + 1;
+      // the epilogue's operands come in behind the last step (the waits above
+      // do not count them)
+      if (!F32 && !EARLY && t + 1 == nk) epi.load(g, c);
+    };
+    for (int t = 0; t < nk; ++t) {
+      arrive(t);
+      const char *sta = lds + sa * OpA::BYTES, *stb = lds + B0 + sb * OpB::BYTES;
+#pragma unroll
+      for (int s = 0; s < Cfg::SL; ++s) {
+        float xa[MB][8], xb[NB][8];
+        la.read(sta, s, xa);
+        lb.read(stb, s, xb);
+        if constexpr (F32) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+#pragma unroll
+            for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+              for (int bj = 0; bj < NB; ++bj)
+                acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[bi][e], xb[bj][e], acc[bi][bj], 0, 0, 0);
+        } else {
+          sp_bf16x8 a[3][MB], b[3][NB];
+          split_frag<MB>(xa, a);
+          split_frag<NB>(xb, b);
+          if (DW && do_bias) {
+#pragma unroll
+            for (int i = 0; i < MB; ++i)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) bsum[i] += xa[i][e];
+          }
+          split_mfma<MB, NB>(a, b, acc, low);
+        }
+      }
+      sa = sa + 1 == NSA ? 0 : sa + 1;
+      sb = sb + 1 == NSB ? 0 : sb + 1;
+    }
+#pragma unroll
+    for (int bi = 0; bi < MB; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < NB; ++bj)
+        if (!F32) acc[bi][bj] += low[bi][bj];
     wait_lgkm0();
     barrier();
-    if (t + NSA - 1 < nk) fire_a(t + NSA - 1, na);
-    if (t + NSB - 1 < nk) fire_b(t + NSB - 1, nb);
-    na = na + 1 == NSA ? 0 : na + 1;
-    nb = nb + 1 == NSB ? 0 : nb + 1;
-    // the epilogue's operands come in behind the last step (the waits above
-    // do not count them)
-    if (!EARLY && t + 1 == nk) epi.load(g, c);
   };
-  for (int t = 0; t < nk; ++t) {
-    arrive(t);
-    const char *sta = lds + sa * OpA::BYTES, *stb = lds + B0 + sb * OpB::BYTES;
-#pragma unroll
-    for (int s = 0; s < Cfg::SL; ++s) {
-      float xa[MB][8], xb[NB][8];
-      la.read(sta, s, xa);
-      lb.read(stb, s, xb);
-      sp_bf16x8 a[3][MB], b[3][NB];
-      split_frag<MB>(xa, a);
-      split_frag<NB>(xb, b);
-      if (DW && do_bias) {
-#pragma unroll
-        for (int i = 0; i < MB; ++i)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) bsum[i] += xa[i][e];
-      }
-      split_mfma<MB, NB>(a, b, acc, low);
-    }
-    sa = sa + 1 == NSA ? 0 : sa + 1;
-    sb = sb + 1 == NSB ? 0 : sb + 1;
-  }
-#pragma unroll
-  for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-    for (int bj = 0; bj < NB; ++bj) acc[bi][bj] += low[bi][bj];
-  wait_lgkm0();
-  barrier();
+  sweep(std::false_type{});
 
   float* et = reinterpret_cast<float*>(lds);
   using Place = SplitPlace<Cfg, !A_KC, !B_KC>;
@@ -330,7 +351,13 @@ __device__ __forceinline__ void direct_tile(const GemmArgs& g, const int logical
     }
   }
   sp_f32x4 v[Cfg::NC];
-  split_gather<Cfg, Place, A_KC, B_KC>(g, c, et, acc, v);
+  split_gather<Cfg, Place>(c, et, acc, v);
+#pragma unroll
+  for (int i = 0; i < Cfg::NC; ++i) v[i] *= kSplitUnscale;
+  if (__builtin_expect(unexplained<Cfg, A_KC, B_KC>(g, c, et, v), 0)) {
+    sweep(std::true_type{});
+    split_gather<Cfg, Place>(c, et, acc, v);
+  }
   epi.store(g, c, v, gb);
 }
 

@@ -32,7 +32,8 @@
 // Infinities: inf - inf in the split makes NaN where the float32 product
 // would keep an infinity, and results of 2^96 and more (operands of 2^111)
 // leave the range that the factors leave, so a tile with a non-finite result
-// is computed again with float32 MFMAs straight from memory (split_gather).
+// that no NaN operand explains is computed again with float32 MFMAs
+// (direct_tile, unexplained).
 #pragma once
 
 #include "device_common.h"
@@ -274,65 +275,73 @@ struct SplitEpilogue {
 };
 
 // The waves' accumulators to LDS and each thread's chunks back in row order,
-// the KW partial sums added in wave order.  SPLIT: the sums are those of split
-// operands and are scaled back, and a result that is not finite makes the
-// workgroup compute its tile again with float32 MFMAs straight from memory.
-// lds is free when this is called (a barrier lies before).
-template <class Cfg, class Place, bool A_KC, bool B_KC, bool SPLIT = true>
-__device__ __forceinline__ void split_gather(const GemmArgs& g, const SplitCoord<Cfg>& c, float* et,
-                                             sp_f32x16 (&acc)[Cfg::WTM / 32][Cfg::WTN / 32], sp_f32x4 (&v)[Cfg::NC]) {
+// the KW partial sums added in wave order.  lds is free when this is called
+// (a barrier lies before); the sums in it stay until the next barrier.
+template <class Cfg, class Place>
+__device__ __forceinline__ void split_gather(const SplitCoord<Cfg>& c, float* et,
+                                             const sp_f32x16 (&acc)[Cfg::WTM / 32][Cfg::WTN / 32],
+                                             sp_f32x4 (&v)[Cfg::NC]) {
   constexpr int MB = Cfg::WTM / 32, NB = Cfg::WTN / 32, NC = Cfg::NC, KW = Cfg::KW, BM = Cfg::BM, ELD = Cfg::ELD;
-  for (int pass = 0;; ++pass) {
-    float* dst = et + (c.kw * BM + c.wm * Cfg::WTM) * ELD + c.wn * Cfg::WTN;
+  float* dst = et + (c.kw * BM + c.wm * Cfg::WTM) * ELD + c.wn * Cfg::WTN;
 #pragma unroll
-    for (int bi = 0; bi < MB; ++bi)
+  for (int bi = 0; bi < MB; ++bi)
 #pragma unroll
-      for (int bj = 0; bj < NB; ++bj)
+    for (int bj = 0; bj < NB; ++bj)
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-          dst[Place::row(bi, 8 * (r >> 2) + 4 * c.lh + (r & 3)) * ELD + Place::col(bj, c.li)] = acc[bi][bj][r];
-    __syncthreads();
-    float chk = 0.f;
+      for (int r = 0; r < 16; ++r)
+        dst[Place::row(bi, 8 * (r >> 2) + 4 * c.lh + (r & 3)) * ELD + Place::col(bj, c.li)] = acc[bi][bj][r];
+  __syncthreads();
 #pragma unroll
-    for (int i = 0; i < NC; ++i) {
-      const float* src = et + (c.er0 + i * c.ERS) * ELD + c.ecl;
-      v[i] = *reinterpret_cast<const sp_f32x4*>(src);
+  for (int i = 0; i < NC; ++i) {
+    const float* src = et + (c.er0 + i * c.ERS) * ELD + c.ecl;
+    v[i] = *reinterpret_cast<const sp_f32x4*>(src);
 #pragma unroll
-      for (int w = 1; w < KW; ++w) v[i] += *reinterpret_cast<const sp_f32x4*>(src + w * BM * ELD);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) chk += v[i][e] * 0.f;
-    }
-    if (!SPLIT || pass) return;
-#pragma unroll
-    for (int i = 0; i < NC; ++i) v[i] *= kSplitUnscale;
-    if (!__syncthreads_or(chk != 0.f)) return;
-    const int64_t t = g.a.gather || g.b.gather ? gather_step(g.g) : 0;
-#pragma unroll
-    for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < NB; ++bj)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[bi][bj][r] = 0.f;
-    for (int k0 = 2 * c.kw; k0 < g.K; k0 += 2 * KW) {
-      const int k = k0 + c.lh, kc = min(k, g.K - 1);
-      float a[MB], b[NB];
-#pragma unroll
-      for (int bi = 0; bi < MB; ++bi) {
-        a[bi] = operand_at<A_KC>(g.a, g.g, c.worker, t, min(c.m0 + c.wm * Cfg::WTM + Place::row(bi, c.li), g.M - 1), kc);
-        if (k >= g.K) a[bi] = 0.f;
-      }
-#pragma unroll
-      for (int bj = 0; bj < NB; ++bj) {
-        b[bj] = operand_at<B_KC>(g.b, g.g, c.worker, t, min(c.n0 + c.wn * Cfg::WTN + Place::col(bj, c.li), g.N - 1), kc);
-        if (k >= g.K) b[bj] = 0.f;
-      }
-#pragma unroll
-      for (int bi = 0; bi < MB; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < NB; ++bj)
-          acc[bi][bj] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[bi], b[bj], acc[bi][bj], 0, 0, 0);
-    }
+    for (int w = 1; w < KW; ++w) v[i] += *reinterpret_cast<const sp_f32x4*>(src + w * BM * ELD);
   }
+}
+
+// Whether a result of the tile is not finite although no NaN was found in its
+// row of A or its column of B: such a tile has to be computed in float32.  A
+// result with a NaN operand is NaN either way, so that the rounds of a model
+// that has diverged to NaN run at their ordinary speed; NaNs are looked for
+// at kNanProbes k of every row and column (the update of a layer spreads one
+// over a whole row of its weights; a NaN that is not found costs the tile its
+// second pass, nothing else).  8 x 784-1000-1000-10, m = 128, us per round:
+// finite 1979; all weights NaN 2035; one weight in 5488 NaN 2528 (with every
+// such tile computed again by loads straight from memory: 4676 in both).
+// lds is free when this returns.
+constexpr int kNanProbes = 16;
+
+template <class Cfg, bool A_KC, bool B_KC>
+__device__ __forceinline__ bool unexplained(const GemmArgs& g, const SplitCoord<Cfg>& c, float* et,
+                                            const sp_f32x4 (&v)[Cfg::NC]) {
+  float chk = 0.f;
+#pragma unroll
+  for (int i = 0; i < Cfg::NC; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) chk += v[i][e] * 0.f;
+  if (__builtin_expect(!__syncthreads_or(chk != 0.f), 1)) return false;
+  static_assert(Cfg::BM + Cfg::BN <= Cfg::NTH, "a row or a column per thread");
+  if (c.tid < Cfg::BM + Cfg::BN) {
+    const bool row = c.tid < Cfg::BM;
+    const int64_t t = g.a.gather || g.b.gather ? gather_step(g.g) : 0;
+    const int o = row ? min(c.m0 + c.tid, g.M - 1) : min(c.n0 + c.tid - Cfg::BM, g.N - 1);
+    float sum = 0.f;
+    for (int p = 0; p < kNanProbes; ++p) {
+      const int64_t k = (int64_t)g.K * p / kNanProbes;
+      const float x = row ? operand_at<A_KC>(g.a, g.g, c.worker, t, o, k) : operand_at<B_KC>(g.b, g.g, c.worker, t, o, k);
+      sum += x != x ? 1.f : 0.f;
+    }
+    et[c.tid] = sum;
+  }
+  __syncthreads();
+  bool open = false;
+#pragma unroll
+  for (int i = 0; i < Cfg::NC; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      open = open || (v[i][e] * 0.f != 0.f && et[c.er0 + i * c.ERS] == 0.f && et[Cfg::BM + c.ecl + e] == 0.f);
+  return __syncthreads_or(open);
 }
 
 // the six piece products of one slice of 16 k (see the top of this file)

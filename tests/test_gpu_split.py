@@ -90,3 +90,74 @@ def test_infinities_and_largest_values_stay_what_they_are():
         ok = np.isfinite(row_loss)
         np.testing.assert_allclose(rl[ok], row_loss[ok], rtol=1e-4, atol=1e-5)
         g.close()
+
+
+@pytest.mark.parametrize("rows,width", [(70, 40), (8200, 40), (16300, 200)], ids=["small", "flat", "mid"])
+def test_infinity_beside_nan(rows, width):
+    """A unit whose weights are all NaN (its results are NaN whichever way they
+    are computed) beside one with an infinite weight, which has to stay an
+    infinity where its input is positive, and beside a unit with a single NaN
+    between the places that are looked at."""
+    import torch
+
+    import paper_1710_02368_amd as agn
+    dims = (20, width, 36, 6)
+    print(rows, dims, flush=True)
+    rng = np.random.default_rng(3)
+    X, y = rng.standard_normal((rows, 20)).astype(np.float32), rng.integers(0, 6, rows).astype(np.int32)
+    p = unflat_params(W.random_params(dims, 7), dims)
+    p[0][0][3] = np.nan
+    p[0][0][7, 14] = np.nan
+    p[0][0][5, 2] = np.inf
+    g = agn.AGN(dims, 2, 1, 0.05, 8, seed=1)
+    flat = np.concatenate([np.concatenate([w.ravel(), b.ravel()]) for w, b in p])
+    g.set_central(torch.from_numpy(flat).cuda())
+    _, rl, _ = g.evaluate(*to_device(X, y), row_outputs=True)
+    g.close()
+    h = X.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        for l, (w, b) in enumerate(p):
+            h = _product(h, w) + b
+            if l < 2:
+                h = np.where(h > 0, h, 0.0)
+        lse = h.max(axis=1) + np.log(np.exp(h - h.max(axis=1, keepdims=True)).sum(axis=1))
+        want = lse - h[np.arange(rows), y]
+    rl = rl.cpu().numpy()
+    ok = X[:, 2] < 0  # (minus infinity before the rectifier)
+    assert not np.any(np.isfinite(rl[~ok])) and not np.any(np.isfinite(want[~ok]))
+    np.testing.assert_allclose(rl[ok], want[ok], rtol=1e-4, atol=1e-5)
+
+
+def _product(h, w):
+    """h w^T in 64 bits with infinities as IEEE has them (a blocked library
+    product may differ: inf * 0 in its padding)."""
+    return np.concatenate([(h[r:r + 256, None, :] * w.astype(np.float64)[None]).sum(axis=2)
+                           for r in range(0, len(h), 256)])
+
+
+def test_a_model_of_nan_keeps_its_speed():
+    """Tiles of NaN weights are not computed twice (2.5 times the round when
+    they were)."""
+    import time
+
+    import torch
+
+    import paper_1710_02368_amd as agn
+    dims, n, m, rows = (784, 1000, 1000, 10), 8, 128, 8 * 1920
+    x = torch.rand(rows, 784, device="cuda", generator=torch.Generator(device="cuda").manual_seed(1))
+    y = torch.zeros(rows, dtype=torch.int32, device="cuda")
+    took = {}
+    for what in ("finite", "nan"):
+        g = agn.AGN(dims, n, 15, 0.001, m, seed=1)
+        if what == "nan":
+            g.set_central(torch.full((g.P,), float("nan"), device="cuda"))
+        times = []
+        for i in range(12):
+            t = time.perf_counter()
+            g.round(x, y, list(range(n)))
+            torch.cuda.synchronize()
+            times.append(time.perf_counter() - t)
+        took[what] = float(np.median(times[2:]))
+        g.close()
+    print(took, flush=True)
+    assert took["nan"] <= 1.6 * took["finite"], took

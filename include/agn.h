@@ -207,9 +207,10 @@ int agn_evaluate(agn_ctx* ctx, const agn_data* data, float* row_loss, int32_t* r
  * twice, the logits when the output layer is not fused (C > 32 or bf16),
  * and per-block partial sums.  AGN_EINVAL (nothing enqueued) when not even
  * 64 rows fit, i.e. a hidden layer wider than about 32,000 units (float32)
- * or 64,000 (bf16).  In AGN_BF16 contexts the bf16 operands of the central
- * variable are the copy the last commit wrote for its worker's pull, so no
- * conversion buffer is needed.
+ * or 64,000 (bf16).  In AGN_BF16 contexts the operands are the bf16 copy of
+ * the central variable that every commit writes beside it, so no conversion
+ * buffer is needed and a captured call, replayed after further rounds,
+ * evaluates the central variable of that moment (agn_evaluate likewise).
  *
  * Every call on one device shares that device's array and leaves its
  * contents behind (each call overwrites what it reads): calls that overlap
@@ -337,7 +338,7 @@ int agn_debug_batch_indices(agn_ctx* ctx, int32_t worker, int64_t step_t,
  * context launches it: flops = 2 * multiply-adds of the class's matrix
  * products; bytes = the memory traffic the class cannot avoid (for the
  * commit: central + n deltas read, n pulled copies + central written,
- * plus the bf16 copies of the pulls in bf16 mode;
+ * plus the bf16 copies of both in bf16 mode;
  * for the classes with the update: the parameters they update read and
  * written once per local step, plus their bf16 shadow written in bf16
  * mode (and, for the hidden layers' backward launches, read by the input

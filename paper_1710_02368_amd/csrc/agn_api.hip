@@ -9,7 +9,7 @@
 //   buf[0,1]  [n][P_pad]        ping-pong parameters of the local steps; on the
 //                               last step the normalized delta (theta_lambda -
 //                               theta_0) / lambda is stored in place of theta
-//   *16       bf16 shadows of snap/buf (bf16 mode: the matrix-product operands)
+//   *16       bf16 shadows of central/snap/buf (bf16 mode: the matrix-product operands)
 //   H[l]      [n][m][ld_l]      hidden activations after ReLU, l = 1..L-1
 //   Z         [n][m][ld_L]      logits
 //   dZ[l]     [n][m][ld_l]      gradients of the batch loss w.r.t. layer inputs, l = 1..L
@@ -58,6 +58,7 @@ struct agn_ctx {
   float* snap = nullptr;
   float* buf[2] = {nullptr, nullptr};
   uint16_t* snap16 = nullptr;
+  uint16_t* central16 = nullptr;
   uint16_t* buf16[2] = {nullptr, nullptr};
   uint16_t* xrows = nullptr;
   int xrow_steps = 0;
@@ -460,6 +461,7 @@ int enqueue_round(agn_ctx* c, const agn_data* d) {
   ca.snap = c->snap;
   ca.delta = c->buf[(c->lam - 1) & 1];
   ca.snap16 = c->snap16;
+  ca.central16 = c->central16;
   ca.order = c->order;
   ca.scale = c->staleness_scaling ? c->commit_scale : nullptr;
   ca.round = c->round_dev;
@@ -567,10 +569,6 @@ int enqueue_eval(agn_ctx* c, const agn_data* d, float* row_loss, int32_t* row_pr
   const int64_t xes = bf ? 2 : 4;
   const Gather rows_as_stored{c->round_dev, c->lam, 0, c->m, 1};  // (no gathered operand)
   const int products = c->use_head ? L - 1 : L;
-  // bf16 operands of the central variable: the copy that the last commit
-  // wrote for the last committer's pull (before the first round, and after
-  // agn_set_central, every worker's copy is the central one)
-  const uint16_t* w16 = bf ? c->snap16 + (int64_t)c->last_committer * c->P_pad : nullptr;
   for (int64_t r0 = 0; r0 < N; r0 += ws.chunk) {
     const int32_t rows = (int32_t)std::min(ws.chunk, N - r0);
     const void* x = static_cast<const char*>(d->x) + r0 * d0 * xes;
@@ -588,7 +586,7 @@ int enqueue_eval(agn_ctx* c, const agn_data* d, float* row_loss, int32_t* row_pr
       g.K = c->dims[l];
       g.batch = 1;
       g.a = l == 0 ? xop : Operand{ws.h[(l - 1) & 1], c->lda[l], 0, 0, 1};
-      g.b = bf ? Operand{w16 + c->woff[l], c->ldw[l], 0, 0, 1}
+      g.b = bf ? Operand{c->central16 + c->woff[l], c->ldw[l], 0, 0, 1}
                : Operand{c->central + c->woff[l], c->ldw[l], 0, 0, 1};
       g.g = rows_as_stored;
       g.epi = l < L - 1 ? EPI_FWD_RELU : EPI_FWD_LINEAR;
@@ -762,7 +760,8 @@ int agn_create(const agn_shapes* shapes, int32_t n, int32_t lambda, float eta, u
             dalloc(c, &c->commit_scale, n) == hipSuccess &&
             dalloc(c, &c->zero, 1024) == hipSuccess && dalloc(c, &c->sink, 1024) == hipSuccess;
   if (ok && bf)
-    ok = dalloc(c, &c->snap16, nps) == hipSuccess && dalloc(c, &c->buf16[0], nps) == hipSuccess &&
+    ok = dalloc(c, &c->central16, c->P_pad) == hipSuccess && dalloc(c, &c->snap16, nps) == hipSuccess &&
+         dalloc(c, &c->buf16[0], nps) == hipSuccess &&
          dalloc(c, &c->buf16[1], nps) == hipSuccess;
   if (ok && bf && c->dims[0] % 8 != 0) {
     const int64_t step = (int64_t)n * c->m * c->lda[0];
@@ -783,6 +782,7 @@ int agn_create(const agn_shapes* shapes, int32_t n, int32_t lambda, float eta, u
   if (e == hipSuccess) e = hipMemset(c->snap, 0, nps * 4);
   if (e == hipSuccess) e = hipMemset(c->buf[0], 0, nps * 4);
   if (e == hipSuccess) e = hipMemset(c->buf[1], 0, nps * 4);
+  if (e == hipSuccess && bf) e = hipMemset(c->central16, 0, c->P_pad * 2);
   if (e == hipSuccess && bf) e = hipMemset(c->snap16, 0, nps * 2);
   if (e == hipSuccess && bf) e = hipMemset(c->buf16[0], 0, nps * 2);
   if (e == hipSuccess && bf) e = hipMemset(c->buf16[1], 0, nps * 2);
@@ -804,7 +804,7 @@ int agn_create(const agn_shapes* shapes, int32_t n, int32_t lambda, float eta, u
   e = hipMalloc(&tmp, P * sizeof(float));
   if (e != hipSuccess) return bail(AGN_ENOMEM, "device allocation failed");
   e = hipMemcpy(tmp, init.data(), P * sizeof(float), hipMemcpyHostToDevice);
-  if (e == hipSuccess) e = launch_unpack(c->pack, tmp, c->central, nullptr, 1, 0, nullptr);
+  if (e == hipSuccess) e = launch_unpack(c->pack, tmp, c->central, c->central16, 1, 0, nullptr);
   if (e == hipSuccess) e = launch_unpack(c->pack, tmp, c->snap, c->snap16, n, c->P_pad, nullptr);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   (void)hipFree(tmp);
@@ -1199,8 +1199,10 @@ int agn_set_state(agn_ctx* c, const void* in, int64_t bytes) {
     HIP_CHECK(c, hipStreamSynchronize(c->stream));
     p += c->P * sizeof(float);
   }
-  if (c->dtype == AGN_BF16)  // the bf16 copies of the pulls, as the commit writes them
+  if (c->dtype == AGN_BF16) {  // the bf16 copies of the pulls and of the central variable, as the commit writes them
     HIP_CHECK(c, launch_copy_bf16(c->snap, c->snap16, (int64_t)c->n * c->P_pad, c->stream));
+    HIP_CHECK(c, launch_copy_bf16(c->central, c->central16, c->P_pad, c->stream));
+  }
   const int64_t rounds = h.rounds;
   HIP_CHECK(c, hipMemcpyAsync(c->round_dev, &rounds, sizeof(rounds), hipMemcpyHostToDevice, c->stream));
   HIP_CHECK(c, hipStreamSynchronize(c->stream));
@@ -1219,7 +1221,7 @@ int agn_set_central(agn_ctx* c, const float* in) {
   if (!in) return fail(c, AGN_EINVAL, "in is NULL");
   if (c->rounds != 0) return fail(c, AGN_ESTATE, "agn_set_central is allowed only before the first round");
   if (int r = set_device(c)) return r;
-  HIP_CHECK(c, launch_unpack(c->pack, in, c->central, nullptr, 1, 0, c->stream));
+  HIP_CHECK(c, launch_unpack(c->pack, in, c->central, c->central16, 1, 0, c->stream));
   HIP_CHECK(c, launch_unpack(c->pack, in, c->snap, c->snap16, c->n, c->P_pad, c->stream));
   HIP_CHECK(c, hipStreamSynchronize(c->stream));
   return AGN_OK;
@@ -1313,9 +1315,9 @@ int agn_kernel_class_work(agn_ctx* c, int32_t cls, double* flops, double* bytes)
       }
       break;
     case AGN_K_COMMIT:
-      // central + n deltas in, n pulls + central out (+ the bf16 copies of
-      // the pulls, the operands of each worker's next round)
-      b = (8.0 * (double)(c->n + 1) + (c->dtype == AGN_BF16 ? 2.0 * c->n : 0.0)) * c->P;
+      // central + n deltas in, n pulls + central out (+ their bf16 copies, the
+      // operands of each worker's next round and of evaluations)
+      b = (8.0 + (c->dtype == AGN_BF16 ? 2.0 : 0.0)) * (double)(c->n + 1) * c->P;
       break;
     case AGN_K_EVAL: {  // the last evaluation: inputs and weights read, logits written
       const double N = (double)c->eval_N;

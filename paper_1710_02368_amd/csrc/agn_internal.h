@@ -203,6 +203,7 @@ struct CommitArgs {
   float* snap;             // [n][P_pad] pulled copies (written)
   const float* delta;      // [n][P_pad] normalized deltas of the round
   uint16_t* snap16;        // bf16 shadow of the pulled copies (or null)
+  uint16_t* central16;     // bf16 copy of the central variable (null where snap16 is)
   const int32_t* order;    // device, n entries
   const float* scale;      // device, n factors by commit position (null: unscaled commits)
   int64_t* round;          // device round counter (incremented)

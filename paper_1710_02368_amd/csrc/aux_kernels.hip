@@ -119,7 +119,10 @@ __global__ __launch_bounds__(256) void commit_kernel(CommitArgs a) {
   }
 #pragma unroll
   for (int u = 0; u < EPT; ++u)
-    if (ok[u]) put<NT>(&central[e0 + 64 * u], c[u]);
+    if (ok[u]) {
+      put<NT>(&central[e0 + 64 * u], c[u]);
+      if (snap16) put<NT>(&reinterpret_cast<u32x2*>(a.central16)[e0 + 64 * u], bf16x4(c[u]));
+    }
   if (blockIdx.x == 0 && threadIdx.x == 0) *a.round += 1;
 }
 

@@ -341,3 +341,44 @@ def test_accumulated_commits_fail_to_converge_where_agn_does():
     assert np.all(np.diff(agn_l) < 0), agn_l
     assert not np.all(np.diff(acc_l) < 0), acc_l
     assert acc_l[-1] > 1.5 * agn_l[-1] and acc_l.mean() > 1.5 * agn_l.mean(), (agn_l, acc_l)
+
+
+@pytest.mark.parametrize("name", ["agn_evaluate", "agn_evaluate_noalloc"])
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_a_captured_evaluation_follows_the_central_variable(name, dtype):
+    """An evaluation captured once and replayed between rounds, each with
+    another worker committing last, gives the eager evaluation's rows of the
+    central variable of that moment."""
+    agn = _agn()
+    import torch
+
+    from paper_1710_02368_amd import agn as binding
+    dims, rows = (64, 96, 40), 700
+    wl = W.small_workload("captured", dims, 3, 2, 40, 0.1, 4, rows, dtype=dtype)
+    X, y = W.make_data(wl)
+    xd, yd = to_device(X, y)
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        g = agn.AGN(dims, 3, 2, 0.1, 40, seed=3, dtype=dtype)
+        rl = torch.zeros(rows, dtype=torch.float32, device="cuda")
+        rp = torch.zeros(rows, dtype=torch.int32, device="cuda")
+        fn = getattr(binding, name)
+        fn(g.ctx, xd, yd, rows, g.dtype, rl, rp)  # (allocates the workspace)
+        stream.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            fn(g.ctx, xd, yd, rows, g.dtype, rl, rp, want_result=False)
+        seen = []
+        for order in (None, [1, 2, 0], [0, 2, 1], [0, 1, 2]):
+            if order:
+                g.round(xd, yd, order)
+            graph.replay()
+            stream.synchronize()
+            replayed = rl.cpu().numpy(), rp.cpu().numpy()
+            rl.fill_(-1.0), rp.fill_(-1)
+            fn(g.ctx, xd, yd, rows, g.dtype, rl, rp)
+            np.testing.assert_array_equal(replayed[0], rl.cpu().numpy(), err_msg=str(order))
+            np.testing.assert_array_equal(replayed[1], rp.cpu().numpy(), err_msg=str(order))
+            seen.append(replayed[0])
+        assert all(np.any(a != b) for a, b in zip(seen, seen[1:]))
+        g.close()

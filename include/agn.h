@@ -89,7 +89,11 @@ typedef struct {
  * weights N(0, 2/d_in) from a SplitMix64 stream through Box-Muller, biases
  * zero) and gives every worker a copy of it (Algorithm 1, first pull).
  * n in [1, AGN_MAX_WORKERS]; lambda >= 1 local steps; eta finite learning
- * rate (constant: Section 4 applies no decay).  *out receives the context
+ * rate (constant: Section 4 applies no decay).  AGN_BF16 contexts whose
+ * data rows fit no 16-byte load (a first width that is no multiple of 8)
+ * also hold aligned copies of the mini-batches of a few local steps: at most
+ * 256 MiB, or those of one step up to 2 GiB; where they are larger or cannot
+ * be allocated the rows are read where they lie, with the same results.  *out receives the context
  * (NULL on failure). */
 int agn_create(const agn_shapes* shapes, int32_t n, int32_t lambda, float eta,
                uint64_t seed, agn_ctx** out);
@@ -183,9 +187,10 @@ typedef struct {
  * Rows go through the forward pass 8192 at a time (float32: 16384 while the
  * activations stay under 1 GiB) in the evaluation's own workspace, which the
  * first call that needs a part of it allocates (activations of that many
- * rows, two buffers of the widest hidden layer; in AGN_BF16 contexts an
- * aligned copy of data rows that no 16-byte load fits; AGN_ENOMEM if that
- * fails) and no round touches: a call between rounds changes nothing a round reads.  It
+ * rows, two buffers of the widest hidden layer; AGN_ENOMEM if that fails; in
+ * AGN_BF16 contexts also an aligned copy, up to 2 GiB, of data rows that no
+ * 16-byte load fits, without which they are read where they lie) and no
+ * round touches: a call between rounds changes nothing a round reads.  It
  * works before the first round (the initial model).  With out != NULL the
  * call waits for the stream; with out == NULL it returns after enqueueing. */
 int agn_evaluate(agn_ctx* ctx, const agn_data* data, float* row_loss, int32_t* row_pred,

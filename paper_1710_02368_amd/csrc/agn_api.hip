@@ -15,8 +15,8 @@
 //   dZ[l]     [n][m][ld_l]      gradients of the batch loss w.r.t. layer inputs, l = 1..L
 //   loss      [n][lambda][m]    per-row cross-entropy of the last round
 //   xrows     [steps][n][m][ld_0]  bf16 mode with data rows that no 16-byte load
-//                               fits: aligned copies of the mini-batches (of the
-//                               whole round, or of one step where that is large)
+//                               fits: aligned copies of the mini-batches of as
+//                               many steps as row_copies.h says
 // Step i of a round reads its weights from src = (i == 0 ? snap : buf[(i-1)%2])
 // and writes dst = buf[i%2]; reading and writing different buffers lets the
 // input-gradient and weight-gradient products of one layer run in either
@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "agn_internal.h"
+#include "row_copies.h"
 #include "../../include/agn.h"
 
 using namespace agn;
@@ -119,10 +120,6 @@ thread_local LaunchEvents g_launch_events{nullptr, nullptr};
 }
 
 namespace {
-
-// aligned copies of a whole round's mini-batches are made by one launch up to
-// this size (256 MiB), step by step beyond
-constexpr int64_t kXrowElements = (int64_t)1 << 27;
 
 inline int64_t round_up(int64_t v, int64_t a) { return (v + a - 1) / a * a; }
 
@@ -505,11 +502,14 @@ int eval_alloc(agn_ctx* c) {
     if (!c->ev_h[i]) ok = dalloc(c, &p, chunk * wmax * act) == hipSuccess, c->ev_h[i] = p;
   }
   if (ok && !c->use_head && !c->ev_z) ok = dalloc(c, &c->ev_z, chunk * c->lda[c->L]) == hipSuccess;
-  if (ok && c->xrows && !c->ev_x) ok = dalloc(c, &c->ev_x, chunk * c->lda[0]) == hipSuccess;
   if (ok && !c->ev_part) ok = dalloc(c, &c->ev_part, 2 * blocks) == hipSuccess;
   double* acc = nullptr;
   if (ok) ok = dalloc(c, &acc, 2) == hipSuccess;
   if (!ok) return fail(c, AGN_ENOMEM, "cannot allocate the evaluation workspace");
+  // (optional, like the round's copies)
+  if (bf && c->dims[0] % 8 != 0 && chunk * c->lda[0] <= kRowCopyMost &&
+      dalloc(c, &c->ev_x, chunk * c->lda[0]) != hipSuccess)
+    (void)hipGetLastError();
   c->ev_acc = acc;  // (set last: marks the workspace complete)
   return AGN_OK;
 }
@@ -763,11 +763,6 @@ int agn_create(const agn_shapes* shapes, int32_t n, int32_t lambda, float eta, u
     ok = dalloc(c, &c->central16, c->P_pad) == hipSuccess && dalloc(c, &c->snap16, nps) == hipSuccess &&
          dalloc(c, &c->buf16[0], nps) == hipSuccess &&
          dalloc(c, &c->buf16[1], nps) == hipSuccess;
-  if (ok && bf && c->dims[0] % 8 != 0) {
-    const int64_t step = (int64_t)n * c->m * c->lda[0];
-    c->xrow_steps = step * lambda <= kXrowElements ? lambda : 1;
-    ok = dalloc(c, &c->xrows, step * c->xrow_steps) == hipSuccess;
-  }
   for (int l = 1; ok && l <= L; ++l) {
     char* p = nullptr;
     const int64_t bytes = (int64_t)n * c->m * c->lda[l] * act;
@@ -809,6 +804,12 @@ int agn_create(const agn_shapes* shapes, int32_t n, int32_t lambda, float eta, u
   if (e == hipSuccess) e = hipDeviceSynchronize();
   (void)hipFree(tmp);
   if (e != hipSuccess) return bail(AGN_EHIP, std::string("init: ") + hipGetErrorString(e));
+  // last, and optional: without a copy the products read the data rows where they lie
+  if (bf && c->dims[0] % 8 != 0) {
+    const int64_t step = (int64_t)n * c->m * c->lda[0];
+    c->xrow_steps = row_copy_steps(step, lambda);
+    if (c->xrow_steps && dalloc(c, &c->xrows, step * c->xrow_steps) != hipSuccess) (void)hipGetLastError();
+  }
   *out = c;
   return AGN_OK;
 }

@@ -3,14 +3,16 @@
 // hands back no context), the error path of a context that cannot reach a
 // device (everything allocated on the host is freed), calls on a NULL
 // context, and the temporal efficiency of Eq. 4 (host arithmetic) on curves
-// with closed-form areas and on malformed curves.  Built against a
-// host-only build of the library; no kernel is launched.
+// with closed-form areas and on malformed curves, and the size of the copies
+// of data rows.  Built against a host-only build of the library; no kernel is
+// launched.
 #include <cmath>
 #include <cstdio>
 #include <cstring>
 #include <vector>
 
 #include "agn.h"
+#include "row_copies.h"
 
 static int failures = 0;
 #define CHECK(cond)                                                          \
@@ -138,10 +140,29 @@ static void check_temporal_efficiency() {
   CHECK(agn_temporal_efficiency(ta, fa, 2, ta, fa, 2, nullptr) == AGN_EINVAL);
 }
 
+static void check_row_copies() {
+  using agn::row_copy_steps;
+  const int64_t fit = agn::kRowCopyElements, most = agn::kRowCopyMost;
+  CHECK(row_copy_steps(8, 15) == 15);
+  CHECK(row_copy_steps(fit / 4, 4) == 4);
+  CHECK(row_copy_steps(fit / 4, 5) == 4);      // as many steps as fit, not one
+  CHECK(row_copy_steps(fit / 4 + 1, 5) == 3);
+  CHECK(row_copy_steps(fit, 3) == 1);
+  CHECK(row_copy_steps(fit + 8, 3) == 1);
+  CHECK(row_copy_steps(most, 3) == 1);
+  CHECK(row_copy_steps(most + 8, 3) == 0);     // no copy
+  for (int64_t step = 8; step <= 4 * most; step = step * 3 + 8)
+    for (int lam = 1; lam <= 1 << 20; lam *= 7) {
+      const int s = row_copy_steps(step, lam);
+      CHECK(s >= 0 && s <= lam && s * step <= std::max(fit, std::min(step, most)));
+    }
+}
+
 int main() {
   check_create();
   check_null_context();
   check_temporal_efficiency();
+  check_row_copies();
   std::printf("host ABI checks: %d failure(s)\n", failures);
   return failures ? 1 : 0;
 }

@@ -58,7 +58,7 @@ def build(out_dir):
     run([CLANG, "-shared", "-fPIC", *san, *objs, *kernel_objs, "-L", os.path.join(ROCM, "lib"), "-lamdhip64",
          "-Wl,-rpath," + os.path.join(ROCM, "lib"), "-o", lib])
     exe = os.path.join(out_dir, "abi_host_checks")
-    run([CLANG, "-g", "-O1", "-std=c++17", "-fno-omit-frame-pointer", *san, "-I", os.path.join(ROOT, "include"),
+    run([CLANG, "-g", "-O1", "-std=c++17", "-fno-omit-frame-pointer", *san, "-I", os.path.join(ROOT, "include"), "-I", CSRC,
          os.path.join(HERE, "abi_host_checks.cpp"), "-L", out_dir, "-lagn_san", "-Wl,-rpath," + out_dir,
          "-Wl,-rpath," + rt, "-o", exe])
     return exe

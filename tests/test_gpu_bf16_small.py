@@ -1,13 +1,13 @@
 """The small-tile bf16 products at the edges of their tiles, against the
 oracle: K that is no multiple of 8 or of a step, ragged rows and columns,
 data rows that no 16-byte load fits (copied into aligned rows for a whole
-round, or step by step where that is large), batches that wrap round their
+round, or for as many steps as fit where that is large), batches that wrap round their
 shard or exceed it."""
 import numpy as np
 import pytest
 
 import workloads as W
-from oracle import AGNOracle
+from oracle import AGNOracle, evaluate
 from tests.helpers import rel_err, to_device
 
 pytestmark = pytest.mark.gpu
@@ -20,7 +20,7 @@ CASES = {
     "quad": ((72, 517, 259, 37), 16, 2, 77, 16 * 100),         # 64 x 64 tiles, wraps round the shard
     "unaligned_quad": ((123, 517, 259, 37), 16, 2, 77, 16 * 100),
     "batch_over_shard": ((48, 70, 66, 10), 2, 2, 50, 60),      # m = 50 rows of shards of 30
-    "rows_step_by_step": ((3071, 16, 5), 2, 90, 256, 600),     # a round's rows exceed the copy's bound
+    "rows_in_two_copies": ((3071, 16, 5), 2, 90, 256, 600),    # a round's rows exceed the copy's bound
 }
 BF16_TOL = 2e-2  # the stated bound of bf16 central variables
 
@@ -49,6 +49,29 @@ def test_bf16_round_matches_oracle(case, adam):
     # the round's total step in the 2-norm: bf16 deltas differ by up to 9e-2
     init = o.__class__(dims, n, lam, wl.eta, m, seed=3, bf16=True).central_flat().astype(np.float64)
     assert np.linalg.norm(got - ref.astype(np.float64)) <= 0.1 * np.linalg.norm(ref - init)
+    g.close()
+
+
+def test_rows_beyond_the_copies_bound_are_read_where_they_lie():
+    """One step's mini-batches of 2.1 GiB: the context holds no copy of them,
+    and the losses are those of the initial model."""
+    import torch
+
+    import paper_1710_02368_amd as agn
+    dims, n, m, S = (4097, 8, 4), 64, 4096, 33
+    wl = W.small_workload("no_copy", dims, n, 1, m, 0.05, 1, n * S, dtype="bf16")
+    X, y = W.make_data(wl)
+    xd, yd = to_device(X, y)
+    before = torch.cuda.mem_get_info()[0]
+    g = agn.AGN(dims, n, 1, 0.05, m, seed=3, dtype="bf16")
+    held = before - torch.cuda.mem_get_info()[0]
+    print("held", held, flush=True)
+    assert held < 1 << 29, held
+    g.round(xd, yd, list(range(n)))
+    row_loss = evaluate(AGNOracle(dims, n, 1, 0.05, m, seed=3, bf16=True).central, X, y, bf16=True)[0]
+    want = np.array([np.resize(row_loss[k * S:(k + 1) * S], m).mean() for k in range(n)])
+    np.testing.assert_allclose(g.loss().cpu().numpy(), want, rtol=5e-3)
+    assert np.all(np.isfinite(g.central().cpu().numpy()))
     g.close()
 
 

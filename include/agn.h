@@ -184,10 +184,11 @@ typedef struct {
  *   row_pred: DEVICE, num_samples int32, or NULL.
  *   out:      HOST, or NULL.  The mean loss is summed in float64 in a
  *             fixed order: repeated calls give identical results.
- * Rows go through the forward pass 8192 at a time (float32: 16384 while the
- * activations stay under 1 GiB) in the evaluation's own workspace, which the
+ * Rows go through the forward pass 8192 at a time (float32: 16384 where the
+ * activations and logits stay under 1 GiB and can be allocated) in the evaluation's own workspace, which the
  * first call that needs a part of it allocates (activations of that many
- * rows, two buffers of the widest hidden layer; AGN_ENOMEM if that fails; in
+ * rows, two buffers of the widest hidden layer, and their logits where the
+ * output layer is not fused; AGN_ENOMEM if that fails for 8192; in
  * AGN_BF16 contexts also an aligned copy, up to 2 GiB, of data rows that no
  * 16-byte load fits, without which they are read where they lie) and no
  * round touches: a call between rounds changes nothing a round reads.  It

@@ -94,9 +94,10 @@ struct agn_ctx {
   float* mom_m = nullptr;  // Adam moment estimates [n][P_pad] (allocated on selection)
   float* mom_v = nullptr;
   // evaluation workspace (allocated by the first agn_evaluate call)
-  void* ev_h[2] = {nullptr, nullptr};  // activations of EVAL_CHUNK rows, ping-pong
-  float* ev_z = nullptr;               // logits of EVAL_CHUNK rows (unfused output layer)
-  uint16_t* ev_x = nullptr;            // aligned copies of EVAL_CHUNK data rows (bf16, rows that no 16-byte load fits)
+  int64_t ev_chunk = 0;                // rows at a time
+  void* ev_h[2] = {nullptr, nullptr};  // activations of ev_chunk rows, ping-pong
+  float* ev_z = nullptr;               // logits of ev_chunk rows (unfused output layer)
+  uint16_t* ev_x = nullptr;            // aligned copies of ev_chunk data rows (bf16, rows that no 16-byte load fits)
   double* ev_part = nullptr;           // per-block partial sums of one chunk
   double* ev_acc = nullptr;            // loss sum and correct count over all rows
   int64_t eval_N = 0;                  // rows of the last agn_evaluate call
@@ -472,9 +473,10 @@ int enqueue_round(agn_ctx* c, const agn_data* d) {
 // Rows the evaluation takes through its forward pass at a time: large
 // enough that each product of a 1000-wide layer spreads over several
 // workgroups per compute unit.  In float32 twice as many, where that keeps
-// the activations under 1 GiB, so that 10,000 rows are one pass (784-1000-
-// 1000-10: 300 us against 352 in two); in bf16 8192 rows of a
-// 2048-wide layer are one round of 256 x 256 tiles (10,000 would take two).
+// the activations and logits under 1 GiB and they can be allocated, so that
+// 10,000 rows are one pass (784-1000-1000-10: 300 us against 352 in two); in
+// bf16 8192 rows of a 2048-wide layer are one round of 256 x 256 tiles
+// (10,000 would take two).
 constexpr int64_t EVAL_CHUNK = 8192;
 
 // widest row of a hidden layer's activations
@@ -485,30 +487,38 @@ int64_t eval_width(const agn_ctx* c) {
 }
 
 int64_t eval_chunk(const agn_ctx* c) {
-  return c->dtype == AGN_FP32 && 2 * EVAL_CHUNK * eval_width(c) * 2 * 4 <= ((int64_t)1 << 30) ? 2 * EVAL_CHUNK : EVAL_CHUNK;
+  const int64_t row = 2 * eval_width(c) + (c->use_head ? 0 : c->lda[c->L]);  // values per evaluated row
+  return c->dtype == AGN_FP32 && 2 * EVAL_CHUNK * row * 4 <= ((int64_t)1 << 30) ? 2 * EVAL_CHUNK : EVAL_CHUNK;
 }
 
 // The evaluation's own buffers (nothing a round uses), allocated once.
 int eval_alloc(agn_ctx* c) {
   if (c->ev_acc) return AGN_OK;
   const bool bf = c->dtype == AGN_BF16;
-  const int64_t wmax = eval_width(c), chunk = eval_chunk(c);
-  const int64_t act = bf ? 2 : 4;
-  const int64_t blocks = std::max(eval_blocks(chunk), head_eval_blocks(chunk));
-  // (a failed call keeps what it got; the next call allocates the rest)
-  bool ok = true;
-  for (int i = 0; ok && i < 2 && wmax > 0; ++i) {
-    char* p = nullptr;
-    if (!c->ev_h[i]) ok = dalloc(c, &p, chunk * wmax * act) == hipSuccess, c->ev_h[i] = p;
-  }
-  if (ok && !c->use_head && !c->ev_z) ok = dalloc(c, &c->ev_z, chunk * c->lda[c->L]) == hipSuccess;
-  if (ok && !c->ev_part) ok = dalloc(c, &c->ev_part, 2 * blocks) == hipSuccess;
+  const int64_t wmax = eval_width(c), act = bf ? 2 : 4;
+  const size_t held = c->allocs.size();
   double* acc = nullptr;
-  if (ok) ok = dalloc(c, &acc, 2) == hipSuccess;
-  if (!ok) return fail(c, AGN_ENOMEM, "cannot allocate the evaluation workspace");
+  const auto buffers = [&](int64_t chunk) {
+    const int64_t blocks = std::max(eval_blocks(chunk), head_eval_blocks(chunk));
+    bool ok = true;
+    for (int i = 0; ok && i < 2 && wmax > 0; ++i) {
+      char* p = nullptr;
+      ok = dalloc(c, &p, chunk * wmax * act) == hipSuccess, c->ev_h[i] = p;
+    }
+    if (ok && !c->use_head) ok = dalloc(c, &c->ev_z, chunk * c->lda[c->L]) == hipSuccess;
+    if (ok) ok = dalloc(c, &c->ev_part, 2 * blocks) == hipSuccess;
+    if (ok) ok = dalloc(c, &acc, 2) == hipSuccess;
+    if (ok) return c->ev_chunk = chunk, true;
+    (void)hipGetLastError();
+    for (size_t i = held; i < c->allocs.size(); ++i) (void)hipFree(c->allocs[i]);
+    c->allocs.resize(held);
+    return false;
+  };
+  if (!buffers(eval_chunk(c)) && (eval_chunk(c) == EVAL_CHUNK || !buffers(EVAL_CHUNK)))
+    return fail(c, AGN_ENOMEM, "cannot allocate the evaluation workspace");
   // (optional, like the round's copies)
-  if (bf && c->dims[0] % 8 != 0 && chunk * c->lda[0] <= kRowCopyMost &&
-      dalloc(c, &c->ev_x, chunk * c->lda[0]) != hipSuccess)
+  if (bf && c->dims[0] % 8 != 0 && c->ev_chunk * c->lda[0] <= kRowCopyMost &&
+      dalloc(c, &c->ev_x, c->ev_chunk * c->lda[0]) != hipSuccess)
     (void)hipGetLastError();
   c->ev_acc = acc;  // (set last: marks the workspace complete)
   return AGN_OK;
@@ -970,7 +980,7 @@ int agn_evaluate(agn_ctx* c, const agn_data* d, float* row_loss, int32_t* row_pr
   if (int r = set_device(c)) return r;
   if (int r = eval_alloc(c)) return r;
   c->ls = c->stream;
-  const EvalSpace ws{{c->ev_h[0], c->ev_h[1]}, c->ev_z, c->ev_x, c->ev_part, c->ev_acc, eval_chunk(c)};
+  const EvalSpace ws{{c->ev_h[0], c->ev_h[1]}, c->ev_z, c->ev_x, c->ev_part, c->ev_acc, c->ev_chunk};
   if (int r = enqueue_eval(c, d, row_loss, row_pred, ws)) return r;
   c->eval_N = d->num_samples;
   return eval_result(c, ws, d->num_samples, out);

@@ -73,13 +73,20 @@ EVAL_CASES = [
     ("bf16_ragged", (200, 130, 70, 10), 3, 40, 650, "gauss_linear", "bf16"),
     ("bf16_many_classes", (256, 300, 300, 100), 4, 70, 1000, "gauss_linear", "bf16"),
     ("bf16_unaligned_d0", (37, 29, 5), 4, 9, 101, "sparse_teacher2", "bf16"),
-    # more rows than the 8192 the library evaluates at a time
-    ("two_chunks", (200, 130, 70, 10), 3, 40, 8192 + 77, "gauss_linear", "fp32"),
-    ("exact_chunk", (64, 48, 10), 2, 16, 8192, "gauss_linear", "fp32"),
-    ("two_chunks_single_layer", (33, 7), 2, 16, 8193, "gauss_linear", "fp32"),
-    ("two_chunks_many_classes", (60, 50, 40), 3, 24, 9000, "gauss_linear", "fp32"),
+    # more rows than the library evaluates at a time: 16384 in float32, 8192
+    # for hidden layers wider than that and in bf16
+    ("two_chunks_16384", (200, 130, 70, 10), 3, 40, 16384 + 77, "gauss_linear", "fp32"),
+    ("exact_chunk_16384", (64, 48, 10), 2, 16, 16384, "gauss_linear", "fp32"),
+    ("two_chunks_16384_single_layer", (33, 7), 2, 16, 16385, "gauss_linear", "fp32"),
+    ("two_chunks_16384_many_classes", (60, 50, 40), 3, 24, 17000, "gauss_linear", "fp32"),
+    ("two_chunks_8192_wide", (24, 8200, 10), 2, 16, 8192 + 130, "gauss_linear", "fp32"),
+    # ... and float32 sets around 8192 rows
+    ("rows_8269", (200, 130, 70, 10), 3, 40, 8192 + 77, "gauss_linear", "fp32"),
+    ("rows_8192", (64, 48, 10), 2, 16, 8192, "gauss_linear", "fp32"),
+    ("rows_8193_single_layer", (33, 7), 2, 16, 8193, "gauss_linear", "fp32"),
+    ("rows_9000_many_classes", (60, 50, 40), 3, 24, 9000, "gauss_linear", "fp32"),
     ("bf16_two_chunks", (200, 130, 70, 10), 3, 40, 8192 + 555, "gauss_linear", "bf16"),
-    # a full 8192-row chunk of a 2048-wide layer: 256 x 256 forward tiles
+    # bf16: a full 8192-row chunk of a 2048-wide layer: 256 x 256 forward tiles
     ("bf16_big_tiles", (64, 2048, 10), 2, 16, 8192 + 300, "gauss_linear", "bf16"),
 ]
 
@@ -88,8 +95,8 @@ EVAL_CASES = [
 @pytest.mark.parametrize("model", ["initial", "set"])
 def test_evaluate_matches_oracle(case, model):
     """The initial model (same generator on both sides) and a seeded model
-    set on both sides, over sets smaller and larger than the 8192 rows the
-    library evaluates at a time, ragged at the tile and chunk edges."""
+    set on both sides, over sets smaller and larger than what the library
+    evaluates at a time, ragged at the tile and chunk edges."""
     agn = _agn()
     name, dims, n, m, N, data, dtype = case
     wl = W.small_workload(name, dims, n, 2, m, 0.05, 1, N, data=data, dtype=dtype)
@@ -107,6 +114,26 @@ def test_evaluate_matches_oracle(case, model):
     tol = FP32_TOL if dtype == "fp32" else BF16_TOL
     err, close = check_rows(res, rl, rp, X, y, params, dims, dtype, tol)
     print(f"{name}/{model}: row loss err {err:.2e}, near-tie rows {close}, acc {res[1]:.4f}", flush=True)
+    g.close()
+
+
+@pytest.mark.parametrize("dims,limit", [((16, 8, 70000), 3.0e9), ((16, 20000, 10), 1.6e9)], ids=["logits", "hidden"])
+def test_the_workspace_of_a_wide_model_is_that_of_8192_rows(dims, limit):
+    """16384 rows at a time only where activations and logits stay under 1 GiB
+    (2.3 GB of logits and 1.3 GB of activations here at 8192)."""
+    agn = _agn()
+    import torch
+    print(dims, flush=True)
+    x = torch.zeros((40, 16), dtype=torch.float32, device="cuda")
+    y = torch.zeros(40, dtype=torch.int32, device="cuda")
+    g = agn.AGN(dims, 2, 1, 0.05, 8, seed=1)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info()[0]
+    loss = g.evaluate(x, y)[0]
+    held = before - torch.cuda.mem_get_info()[0]
+    print(dims, "held", held, flush=True)
+    assert held < limit, held
+    assert loss == pytest.approx(math.log(dims[-1]), rel=1e-5)  # (all logits zero)
     g.close()
 
 

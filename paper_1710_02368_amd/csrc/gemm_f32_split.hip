@@ -16,16 +16,21 @@
 // or two per compute unit, so a tile's own chain (load latency, 16 K steps of
 // split, MFMAs and a barrier, the gather of the waves' sums); at forty workers
 // of 2000 the matrix pipe (MFMAs and the split's dot products) at 160 TFLOP/s.
-// Kernel times against the float32-MFMA kernels these replaced (us):
-//   forward 8 x 128 x 1000 x 1000 / 784     21.6 (average of both) against 20.8
-//   forward 20 x 128 x 1000 x 1000 / 784    45.6 against 51.8
-//   forward 40 x 128 x 2000 x 2000          256 against 322
-//   backward 8 / 20 x 1000 x 1000 x 128     43.6 against 50.4, 98.5 against 128.6
-//   first layer 8 / 20 x 1000 x 784 x 128   25.5 against 30.0, 59.5 against 66.3
-//   10 x 784-512-256, m = 64                forward 10.2 against 15.0 (average), backward 11.6
-//     against 16.8, first layer 14.6 (with the output layer's update) against 20.3 + 6.4
-//   5 x 123-517-259, m = 50                 forward 8.4 against 21.3, backward 8.2 against 15.6
-//   2 x 784-64, m = 32                      forward 9.9 against 16.4
+// Kernel times against the float32-MFMA kernels these replaced (us, both on
+// one card in turn):
+//   forward 8 x 128 x 1000 x 1000 / 784     21.7 (average of both) against 20.5
+//   forward 20 x 128 x 1000 x 1000 / 784    45.5 against 50.7
+//   forward 40 x 128 x 2000 x 2000          267 against 322
+//   backward 8 / 20 x 1000 x 1000 x 128     43.6 against 49.8, 101.9 against 125.5
+//   first layer 8 / 20 x 1000 x 784 x 128   26.8 against 30.6, 59.8 against 66.1
+//   10 x 784-512-256, m = 64                forward 10.6 against 15.0 (average), backward 11.2
+//     against 18.0, first layer 16.0 (with the output layer's update) against 20.0 + 7.7
+//   5 x 123-517-259, m = 50                 forward (with the logits) 7.8 against 15.2, backward
+//     (average of two) 7.4 against 13.5
+// Two kinds of launches are slower than the float32-MFMA kernels were, where
+// the split's vector work is not hidden: forward products of about 256 64 x 64
+// tiles (5 %, above), and backward launches of 256-wide layers at m = 256
+// (8 x 512 x 256 x 256 18.9 against 18.4).
 #include "head_dw_unit.h"
 #include "split_dl.h"
 
@@ -40,6 +45,7 @@ __host__ __device__ inline int tiles_of(const GemmArgs& g) {
 // Tile shapes (see fwd, launch_gemm_f32_bwd and dw for where each is used)
 using Wide = SplitCfg<64, 64, 2, 1, 2, 1>;   // 128 x 64, two slices per step: a whole mini-batch per weight tile
 using Mid = SplitCfg<64, 64, 1, 1, 4, 1>;    // 64 x 64, four slices
+struct Deep : Mid {};                        // ... with three LDS stages: a tile per compute unit
 using Flat = SplitCfg<32, 64, 1, 1, 4, 1>;   // 32 x 64, four slices
 using Small = SplitCfg<32, 32, 1, 1, 4, 1>;  // 32 x 32, four slices: many tiles of a small product
 using MidW = SplitCfg<32, 32, 2, 2, 1, 2>;   // 64 x 64 as four waves of 32 x 32: weight gradients
@@ -54,6 +60,14 @@ struct Stages<Wide> {
 };
 template <>
 struct Stages<Small> {
+  static constexpr int A = 3, B = 3;
+};
+template <>
+struct Stages<Deep> {
+  static constexpr int A = 3, B = 3;
+};
+template <>
+struct Stages<MidW> {
   static constexpr int A = 3, B = 3;
 };
 
@@ -119,18 +133,25 @@ hipError_t go_fwd(const GemmArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Tile shapes by the product's number of 64 x 64 tiles (us, measured):
-//                              tiles   Small   Flat    Mid
-//   5 x 50 x 517 x 259            45     6.4    7.7   10.2
-//   10 x 64 x 512 x 784           80    11.5   12.5   16.9
-//   8 x 128 x 1000 x 784         256    19.8   17.0   18.3
-//   8 x 128 x 1000 x 1000        256    23.4   20.2   21.8
-//   20 x 128 x 1000 x 1000       640    50.1   44.8   44.8
-//   40 x 128 x 2000 x 2000      2560     385    350    267
-constexpr int kFlatTiles = 128, kMidTiles = 700;
+// Forward tile shapes by the product's number of 64 x 64 tiles (us, measured):
+//                              tiles   Small   Flat   Deep    Mid
+//   10 x 64 x 512 x 784           80    14.2                 19.9
+//   4 x 128 x 1000 x 1000        128    17.6   18.7
+//   6 x 128 x 1000 x 1000        192    24.1   24.7          26.4
+//   8 x 128 x 1000 x 784         256    25.7   22.8          22.6
+//   8 x 128 x 1000 x (784, 1000) 256           22.2   21.7        (average of both)
+//   12 x 128 x 1000 x 784        384    35.0   29.1          32.0
+//   20 x 128 x 1000 x 784        640    54.3   43.7          46.6
+//   24 x 128 x 1000 x 784        768           50.0          47.9
+//   28 x 128 x 1000 x 784        896           56.4          56.1
+// (Deep's 96 KB of LDS leave one workgroup per compute unit, so it ends at a
+// tile per unit.)
+constexpr int kFlatTiles = 200, kDeepTiles = 256, kMidTiles = 700;
 // ... and from this many 128 x 64 tiles on, a tile holds a worker's whole
-// mini-batch and reads each weight once (40 x 128 x 2000 x 2000, 1280 tiles:
-// 255 against 267 us; 20 x 128 x 1000 x 1000, 320 tiles: 52 against 45)
+// mini-batch and reads each weight once (Wide against Mid: 40 x 128 x 2000 x
+// 784, 1280 tiles, 119 us both, and 255 against 267 at 2000 x 2000; 32 x 128 x
+// 2000 x 784, 1024, 99 both; below, Wide wins or loses with how its tiles fill
+// the card: 960 96 against 106, 640 77 against 73, 320 48 against 45)
 constexpr int kWideTiles = 1024;
 
 template <int EPI>
@@ -140,7 +161,8 @@ hipError_t fwd(const GemmArgs& g, hipStream_t s) {
   if (g.batch > 1 && g.M > 64 && tiles_of<Wide>(g) >= kWideTiles) return go_fwd<Wide, EPI>(g, s);
   const int t = tiles_of<Mid>(g);
   if (t >= kMidTiles) return go_fwd<Mid, EPI>(g, s);
-  return t >= kFlatTiles ? go_fwd<Flat, EPI>(g, s) : go_fwd<Small, EPI>(g, s);
+  if (t < kFlatTiles) return go_fwd<Small, EPI>(g, s);
+  return t <= kDeepTiles ? go_fwd<Deep, EPI>(g, s) : go_fwd<Flat, EPI>(g, s);
 }
 
 template <class CX, class CW>
@@ -165,10 +187,19 @@ hipError_t go_dw(const GemmArgs& g, const HeadDwArgs& h, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Weight gradients of at least this many 64 x 64 tiles (10 x 512 x 784 x 64,
-// 1040 tiles: 13.4 us against 19.5 in 32 x 32; 5 x 517 x 259 x 50, 225 tiles:
-// 7.3 against 6.1)
-constexpr int kMidWTiles = 400;
+// Weight gradients of at least this many 64 x 64 tiles go in 64 x 64, fewer in
+// 32 x 32 (us, 64 x 64 against 32 x 32): 20 x 128 x 256 x 64, 160 tiles, 8.6
+// and 8.0; 6 x 128 x 1000 x 128, 192, 11.0 both; 8 x, 256, 11.2 and 12.1; 12 x,
+// 384, 14.0 and 15.5.  Backward launches, 12 x 256 x 256 x 128, 192: 12.6 and
+// 12.4; 16 x, 256: 12.9 and 14.0; 24 x 256 x 256 x 256, 384: 27.2 and 28.1.
+// MidW's third LDS stage: 20 x 1000 x 784 x 128 59.8 against 60.6, backward
+// launch 16 x 256 x 256 x 256 19.2 against 21.4.
+constexpr int kMidWTiles = 220;
+// The input gradient beside them: 32 x 64 tiles from this many 64 x 64 tiles
+// on, 32 x 32 below (us of the launch, 32 x 64 against 32 x 32): 8 x 512 x 512 x
+// 64, 64 tiles, 13.7 and 12.9; 12 x, 96, 17.1 and 17.9; 14 x, 112, 18.9 and 19.9;
+// 8 x 512 x 512 x 128, 128, 17.4 and 19.8.
+constexpr int kFlatDxTiles = 100;
 
 template <int HCM>
 hipError_t dw(const GemmArgs& g, const HeadDwArgs& h, hipStream_t s) {
@@ -190,7 +221,7 @@ hipError_t launch_gemm_f32_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream
   if (dx.epi != EPI_DX_MASK || dw.epi != EPI_DW_UPDATE) return hipErrorInvalidValue;
   if (gemm_f32_strip_ok(dx, dw)) return launch_gemm_f32_strip_bwd(dx, dw, s);
   if (tiles_of<MidW>(dw) < kMidWTiles) return go_bwd<Small, Small>(dx, dw, s);
-  return tiles_of<Mid>(dx) >= kFlatTiles ? go_bwd<Flat, MidW>(dx, dw, s) : go_bwd<Small, MidW>(dx, dw, s);
+  return tiles_of<Mid>(dx) >= kFlatDxTiles ? go_bwd<Flat, MidW>(dx, dw, s) : go_bwd<Small, MidW>(dx, dw, s);
 }
 
 bool gemm_f32_dw_head_ok(const HeadDwArgs& h) { return h.C >= 1 && h.C <= 10 && h.n >= 1 && h.d >= 1; }

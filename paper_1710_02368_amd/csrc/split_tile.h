@@ -51,7 +51,7 @@ typedef uint32_t sp_u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kSplitScale = 0x1p16f, kSplitUnscale = 0x1p-32f;  // of an operand; of a product of two
 
-// eight float32 values -> the three bf16 pieces of 2^23 times each, 16 bytes each
+// eight float32 values -> the three bf16 pieces of 2^16 times each, 16 bytes each
 __device__ __forceinline__ void split8(const float (&x)[8], sp_u32x4& h, sp_u32x4& m, sp_u32x4& l) {
   // (-1, 0) and (0, -1), the first from a register: the compiler would encode
   // it as the inline constant -1.0, which the instruction reads as (0, -1)

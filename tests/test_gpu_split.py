@@ -18,6 +18,8 @@ CASES = {
     "flat_midw": ((130, 514, 66, 10), 16, 70, 16 * 90),         # 32 x 64 forward, 64 x 64 weight gradient, m > 64
     "flat_midw_unaligned": ((131, 514, 66, 12), 16, 70, 16 * 90),
     "flat_bwd": ((64, 260, 514, 10), 16, 70, 16 * 90),          # 32 x 64 input gradient beside 64 x 64 weight tiles
+    "deep": ((132, 450, 66, 10), 16, 70, 16 * 90),              # 64 x 64 forward, three stages
+    "deep_unaligned": ((131, 450, 66, 10), 16, 70, 16 * 90),
     "mid": ((68, 385, 33, 10), 40, 130, 40 * 200),              # 64 x 64 forward
     "wide": ((36, 700, 33, 10), 48, 130, 48 * 200),             # 128 x 64 forward, the second row tile of 2 rows
     "wide_unaligned": ((37, 700, 33, 10), 48, 130, 48 * 200),
@@ -92,7 +94,8 @@ def test_infinities_and_largest_values_stay_what_they_are():
         g.close()
 
 
-@pytest.mark.parametrize("rows,width", [(70, 40), (8200, 40), (16300, 200)], ids=["small", "flat", "mid"])
+@pytest.mark.parametrize("rows,width", [(70, 40), (7000, 70), (16300, 70), (16300, 200)],
+                         ids=["small", "deep", "flat", "mid"])
 def test_infinity_beside_nan(rows, width):
     """A unit whose weights are all NaN (its results are NaN whichever way they
     are computed) beside one with an infinite weight, which has to stay an

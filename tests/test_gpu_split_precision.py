@@ -42,7 +42,9 @@ def forward_shape(n, m, out):
     if n > 1 and m > 64 and tiles(n, m, out, 128) >= rule("kWideTiles"):
         return "wide"
     t = tiles(n, m, out)
-    return "mid" if t >= rule("kMidTiles") else "flat" if t >= rule("kFlatTiles") else "small"
+    if t >= rule("kMidTiles"):
+        return "mid"
+    return "small" if t < rule("kFlatTiles") else "deep" if t <= rule("kDeepTiles") else "flat"
 
 
 def dw_shape(n, out, inp):
@@ -52,7 +54,7 @@ def dw_shape(n, out, inp):
 def bwd_shape(n, m, out, inp):
     if dw_shape(n, out, inp) == "small":
         return "small"
-    return "flat+midw" if tiles(n, m, inp) >= rule("kFlatTiles") else "small+midw"
+    return "flat+midw" if tiles(n, m, inp) >= rule("kFlatDxTiles") else "small+midw"
 
 
 def structured(rng, shape, e):
@@ -103,8 +105,11 @@ TWO_LAYERS = {
     "small": ((100, 70, 10), 2, 32, "small", "small"),
     "small_unaligned": ((101, 70, 10), 2, 32, "small", "small"),
     "small_linear": ((64, 96, 40), 3, 32, "small", "small"),         # (logits by the split product)
-    "flat": ((132, 514, 10), 16, 64, "flat", "midw"),
-    "flat_unaligned": ((131, 514, 10), 16, 64, "flat", "midw"),
+    "small_full": ((132, 514, 10), 16, 64, "small", "midw"),
+    "deep": ((132, 900, 10), 16, 64, "deep", "midw"),
+    "deep_unaligned": ((131, 900, 10), 16, 64, "deep", "midw"),
+    "flat": ((132, 1100, 10), 16, 64, "flat", "midw"),
+    "flat_unaligned": ((131, 1100, 10), 16, 64, "flat", "midw"),
     "mid": ((68, 580, 10), 40, 128, "mid", "midw"),
     "wide": ((36, 900, 10), 40, 256, "wide", "midw"),
     "wide_unaligned": ((37, 900, 10), 40, 256, "wide", "midw"),

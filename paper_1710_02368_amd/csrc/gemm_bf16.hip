@@ -303,9 +303,20 @@ hipError_t go(const GemmArgs& g, hipStream_t s) {
 }  // namespace
 
 // Products of fewer 128 x 128 tiles than this leave compute units idle: small
-// tiles instead, the same sums in the same order (logits of 8192 rows x 100
-// classes over 2048 units, 64 tiles: 17.9 against 20.0 us in 128 x 128)
+// tiles instead, the same sums in the same order.  Small tiles read their
+// operands more often, so that with a long K the line lies lower.  us in small
+// against 128 x 128 tiles (forward over 2048 units, m = 128):
+//   tiles  K = 256       1024          2048          3072          8192
+//     64   11.1  15.3    13.6  20.8    16.6  26.0    19.5  34.0    37.4  59.1
+//    128   11.9  15.6    14.7  21.5    20.9  27.9    29.0  35.3    59.4  67.0
+//    160   13.7  17.5    19.4  21.7    26.8  28.4    36.7  36.3    78.1  69.2
+//    192   14.2  17.8    20.7  22.7    30.1  28.9    41.2  36.7    86.3  73.0
+//    256   14.4  18.0    24.2  23.4                  48.5  39.3    98.8  80.9
+// Weight gradients 192: 12.8 and 15.2, 256: 14.8 and 15.6, 1280: 55.2 and 50.4;
+// backward launches (input and weight gradient) 192: 10.5 and 12.5, 288: 13.2
+// and 14.0, 384: 16.6 and 15.6.
 constexpr int kSmallTiles = 200;
+int small_tiles(int K) { return K < 2048 ? kSmallTiles : K < 4096 ? 168 : 144; }  // forward products
 
 hipError_t launch_gemm_bf16_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s) {
   if (dx.epi != EPI_DX_MASK || dw.epi != EPI_DW_UPDATE) return hipErrorInvalidValue;
@@ -320,7 +331,8 @@ hipError_t launch_gemm_bf16_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStrea
 
 hipError_t launch_gemm_bf16(int a_kc, int b_kc, const GemmArgs& g, hipStream_t s) {
   const bool dl = gemm_bf16_dl_ok(a_kc, b_kc, g);
-  if (gemm_bf16_small_ok(g) && (!dl || tiles_of(g) < kSmallTiles)) return launch_gemm_bf16_small(a_kc, b_kc, g, s);
+  if (gemm_bf16_small_ok(g) && (!dl || tiles_of(g) < (g.epi == EPI_DW_UPDATE ? kSmallTiles : small_tiles(g.K))))
+    return launch_gemm_bf16_small(a_kc, b_kc, g, s);
   if (dl) return launch_gemm_bf16_dl(a_kc, b_kc, g, s);
   if (a_kc && b_kc && g.epi == EPI_FWD_RELU) return go<true, true, EPI_FWD_RELU>(g, s);
   if (a_kc && b_kc && g.epi == EPI_FWD_LINEAR) return go<true, true, EPI_FWD_LINEAR>(g, s);

@@ -1,8 +1,12 @@
-"""The small-tile bf16 products at the edges of their tiles, against the
-oracle: K that is no multiple of 8 or of a step, ragged rows and columns,
+"""The bf16 products at the edges of their tiles, against the oracle.  Small
+tiles: K that is no multiple of 8 or of a step, ragged rows and columns,
 data rows that no 16-byte load fits (copied into aligned rows for a whole
 round, or for as many steps as fit where that is large), batches that wrap round their
-shard or exceed it."""
+shard or exceed it.  128 x 128 tiles (products of enough of them): a K tail,
+a wrapping gather, ragged batches and widths, logits."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -65,8 +69,13 @@ def check_steps(got, ref, init, dims, bound):
 @pytest.mark.parametrize("case", CASES)
 @pytest.mark.parametrize("adam", [None, (0.9, 0.999, 1e-5)], ids=["sgd", "adam"])
 def test_bf16_round_matches_oracle(case, adam):
-    import paper_1710_02368_amd as agn
     dims, n, lam, m, N = CASES[case]
+    assert set(large_products(dims, n, m)) <= {"bwd1"}
+    check_round(case, dims, n, lam, m, N, adam)
+
+
+def check_round(case, dims, n, lam, m, N, adam):
+    import paper_1710_02368_amd as agn
     print(case, dims, n, lam, m, N, adam, flush=True)
     wl = W.small_workload(case, dims, n, lam, m, 0.02 if adam is None else 0.001, 1, N, order="permutation",
                           dtype="bf16")
@@ -89,6 +98,53 @@ def test_bf16_round_matches_oracle(case, adam):
     assert np.linalg.norm(got - ref) <= 0.1 * np.linalg.norm(ref - init)
     check_steps(got, ref, init, dims, STEP_TOL[adam is not None])
     g.close()
+
+
+# dims, n, lambda, m, N, the products that go in 128 x 128 tiles: of every case
+# some forward product, or the first layer's weight gradient, or the backward
+# launch of a layer
+LARGE = {
+    # K = m = 100 with a tail, the third step's mini-batch wraps round the
+    # shard (offsets 0, 100, 200 of 216), ragged rows and columns
+    "gather": ((136, 264, 200, 10), 72, 3, 100, 72 * 216, ("fwd0", "dw0", "bwd1", "bwd2")),
+    "unaligned": ((131, 259, 203, 10), 72, 3, 100, 72 * 216, ("dw0", "bwd1", "bwd2")),
+    # float32 logits of a ragged width, the forward K one step and a half
+    "logits": ((72, 136, 1610), 16, 2, 100, 16 * 120, ("fwd1", "bwd1")),
+    # a long forward K, where fewer tiles are enough
+    "long_k": ((2056, 1100, 10), 20, 1, 100, 20 * 100, ("fwd0", "dw0", "bwd1")),
+    "longer_k": ((4104, 1032, 10), 17, 1, 72, 17 * 72, ("fwd0", "dw0")),
+}
+
+
+def large_products(dims, n, m):
+    """The products in 128 x 128 tiles, by the rules and thresholds that the
+    dispatch states."""
+    path = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_1710_02368_amd", "csrc",
+                        "gemm_bf16.hip")
+    with open(path) as f:
+        src = f.read()
+    few = int(re.search(r"kSmallTiles = (\d+)", src).group(1))
+    mid_k, mid, long_k, most = (int(v) for v in re.search(
+        r"K < (\d+) \? kSmallTiles : K < (\d+) \? (\d+) : (\d+);", src).group(1, 3, 2, 4))
+    t = lambda rows, cols: n * -(-rows // 128) * -(-cols // 128)
+    out = []
+    for l, (k, o) in enumerate(zip(dims, dims[1:])):
+        line = few if k < mid_k else mid if k < long_k else most
+        if k % 8 == 0 and t(m, o) >= line:
+            out.append(f"fwd{l}")
+        if l == 0 and t(o, k) >= few:
+            out.append("dw0")
+        if l > 0 and t(m, k) + t(o, k) >= few:
+            out.append(f"bwd{l}")
+    return out
+
+
+@pytest.mark.parametrize("case", LARGE)
+@pytest.mark.parametrize("adam", [None, (0.9, 0.999, 1e-5)], ids=["sgd", "adam"])
+def test_bf16_round_in_large_tiles_matches_oracle(case, adam):
+    dims, n, lam, m, N, products = LARGE[case]
+    assert set(products) <= set(large_products(dims, n, m)), large_products(dims, n, m)
+    check_round(case, dims, n, lam, m, N, adam)
 
 
 def test_rows_beyond_the_copies_bound_are_read_where_they_lie():

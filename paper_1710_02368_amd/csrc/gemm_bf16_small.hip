@@ -4,9 +4,11 @@
 // multiple of 8).
 //
 // What bounds them is latency: few tiles, each a chain of K steps.  So a tile
-// is 64 x 64 (four waves of 32 x 32) or 32 x 32 (one wave), K goes in steps of
-// 64 with loads three steps ahead, and a wave runs its own K slices in order,
-// one v_mfma_f32_32x32x16_bf16 each -- the sums, and so the results, are those
+// is 64 x 64 (four waves of 32 x 32; 32 x 32 tiles of one wave are slower or
+// even at every count of tiles: backward launch 4 x 512 x 512 x 256 8.2 against
+// 7.4 us, forward 24 x 128 x 512 x 256 8.1 against 7.8), K goes in steps of 64
+// with loads three steps ahead, and a wave runs its own K slices in order, one
+// v_mfma_f32_32x32x16_bf16 each -- the sums, and so the results, are those
 // of the 128 x 128 tiles bit for bit (the bias gradient's, which only the
 // order of its float32 sum changes, aside).  6 workers of 123-517-259-37,
 // m = 77, against the register-staged kernels that took these products before
@@ -22,8 +24,7 @@ typedef __bf16 bs_bf16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) bs_i16x4 lds_bs_i16x4;
 
 using Quad = SplitCfg<32, 32, 2, 2, 1, 4>;  // 64 x 64, four waves
-using One = SplitCfg<32, 32, 1, 1, 1, 4>;   // 32 x 32, one wave
-constexpr int NS16 = 4;                     // LDS stages
+constexpr int NS16 = 4;                    // LDS stages
 
 // Loads and fragments of one operand, OUT outer indices x BK k of bf16 per
 // step.  Rows are 16-byte aligned and zero between their end and the next
@@ -252,14 +253,9 @@ bool operand_aligned(const Operand& op) {
   return op.vec && aligned16(op.ptr) && op.ld % 8 == 0 && op.wstride % 8 == 0;
 }
 
-constexpr int kQuadTiles = 256;  // 64 x 64 tiles from this many on (a tile per compute unit)
-
 template <bool A_KC, bool B_KC, int EPI, bool ADAM>
 hipError_t go(const GemmArgs& g, hipStream_t s) {
-  if (tiles_of<Quad>(g) >= kQuadTiles)
-    AGN_LAUNCH((gemm_bf16_small_kernel<Quad, A_KC, B_KC, EPI, ADAM>), dim3(tiles_of<Quad>(g)), dim3(Quad::NTH), 0, s, g);
-  else
-    AGN_LAUNCH((gemm_bf16_small_kernel<One, A_KC, B_KC, EPI, ADAM>), dim3(tiles_of<One>(g)), dim3(One::NTH), 0, s, g);
+  AGN_LAUNCH((gemm_bf16_small_kernel<Quad, A_KC, B_KC, EPI, ADAM>), dim3(tiles_of<Quad>(g)), dim3(Quad::NTH), 0, s, g);
   return hipGetLastError();
 }
 
@@ -285,18 +281,12 @@ hipError_t launch_gemm_bf16_small(int a_kc, int b_kc, const GemmArgs& g, hipStre
 }
 
 hipError_t launch_gemm_bf16_small_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s) {
-  const bool quad = tiles_of<Quad>(dx) + tiles_of<Quad>(dw) >= kQuadTiles;
-  const auto pad8 = [](int n) { return (n + kNumXcd - 1) / kNumXcd * kNumXcd; };
-  const int n1 = quad ? tiles_of<Quad>(dx) : tiles_of<One>(dx), n1pad = pad8(n1);
-  const dim3 grid(n1pad + (quad ? tiles_of<Quad>(dw) : tiles_of<One>(dw)));
-  if (quad && dw.adam.on)
+  const int n1 = tiles_of<Quad>(dx), n1pad = (n1 + kNumXcd - 1) / kNumXcd * kNumXcd;
+  const dim3 grid(n1pad + tiles_of<Quad>(dw));
+  if (dw.adam.on)
     AGN_LAUNCH((gemm_bf16_small_bwd_kernel<Quad, true>), grid, dim3(Quad::NTH), 0, s, dx, dw, n1, n1pad);
-  else if (quad)
-    AGN_LAUNCH((gemm_bf16_small_bwd_kernel<Quad, false>), grid, dim3(Quad::NTH), 0, s, dx, dw, n1, n1pad);
-  else if (dw.adam.on)
-    AGN_LAUNCH((gemm_bf16_small_bwd_kernel<One, true>), grid, dim3(One::NTH), 0, s, dx, dw, n1, n1pad);
   else
-    AGN_LAUNCH((gemm_bf16_small_bwd_kernel<One, false>), grid, dim3(One::NTH), 0, s, dx, dw, n1, n1pad);
+    AGN_LAUNCH((gemm_bf16_small_bwd_kernel<Quad, false>), grid, dim3(Quad::NTH), 0, s, dx, dw, n1, n1pad);
   return hipGetLastError();
 }
 

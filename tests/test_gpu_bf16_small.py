@@ -18,10 +18,10 @@ pytestmark = pytest.mark.gpu
 
 # dims, n, lambda, m, N
 CASES = {
-    "one_wave": ((104, 37, 70, 12), 2, 2, 20, 400),            # 32 x 32 tiles, forward K = 37
+    "forward_k37": ((104, 37, 70, 12), 2, 2, 20, 400),
     "k_below_a_step": ((8, 33, 5, 3), 3, 3, 7, 100),
     "unaligned": ((101, 71, 60, 40), 2, 3, 20, 400),
-    "quad": ((72, 517, 259, 37), 16, 2, 77, 16 * 100),         # 64 x 64 tiles, wraps round the shard
+    "quad": ((72, 517, 259, 37), 16, 2, 77, 16 * 100),         # wraps round the shard
     "unaligned_quad": ((123, 517, 259, 37), 16, 2, 77, 16 * 100),
     "batch_over_shard": ((48, 70, 66, 10), 2, 2, 50, 60),      # m = 50 rows of shards of 30
     "rows_in_two_copies": ((3071, 16, 5), 2, 90, 256, 600),    # a round's rows exceed the copy's bound

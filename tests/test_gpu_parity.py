@@ -69,14 +69,13 @@ SMALL = [
     ("bf16_many_classes", (256, 300, 300, 100), 4, 2, 70, 0.01, 2, 1000, "gauss_linear", "permutation", "bf16"),
     ("bf16_unaligned_d0", (37, 29, 5), 4, 2, 9, 0.1, 3, 101, "sparse_teacher2", "permutation", "bf16"),
     ("bf16_sgd_n1_lam1", (64, 150, 3), 1, 1, 130, 0.05, 3, 300, "gauss_linear", "sequential", "bf16"),
-    # direct-load products with ragged 64-tiles: the persistent weight-gradient
-    # schedule needs K = m >= 97 (four K steps) and widths divisible by 4
+    # small tiles with ragged edges and several K steps (m = 100)
     ("dl_ragged", (100, 200, 136, 10), 3, 3, 100, 0.05, 3, 650, "sparse_teacher2", "permutation", "fp32"),
     ("bf16_dl_ragged", (100, 200, 136, 10), 3, 3, 100, 0.05, 2, 650, "sparse_teacher2", "permutation", "bf16"),
-    # bf16 direct-load products on every layer but the output layer's
-    # backward: ragged 128-tiles, a K tail (m = 100), the first layer's
-    # weight gradient over gathered rows whose mini-batch wraps round the
-    # shard's end (S = 216: steps at offsets 0, 100, 200)
+    # ragged tiles, a K tail (m = 100), the first layer's weight gradient over
+    # gathered rows whose mini-batch wraps round the shard's end (S = 216:
+    # steps at offsets 0, 100, 200); the same in 128 x 128 tiles, at 72
+    # workers, is in test_gpu_bf16_small.py
     ("bf16_dl_gather", (136, 264, 200, 10), 3, 3, 100, 0.05, 2, 650, "sparse_teacher2", "permutation", "bf16"),
     # 256 x 256 forward tiles (a whole 256-row mini-batch per workgroup,
     # used from 256 tiles on): a hidden layer with a K tail, and the logits.
@@ -86,7 +85,7 @@ SMALL = [
     # between the oracle's own float32 and float64 products.)
     ("bf16_big_tiles", (520, 4096, 10), 16, 2, 256, 0.05, 1, 8192, "sparse_teacher2", "permutation", "bf16"),
     ("bf16_big_logits", (64, 264, 4096), 16, 2, 256, 0.05, 1, 8192, "gauss_linear", "permutation", "bf16"),
-    # (Adam through the same kernels, at small widths: Adam's first step is
+    # (Adam through the small tiles, at small widths: Adam's first step is
     # +-eta times the sign of the gradient, and on wider layers some
     # component's gradient cancels to the rounding level, where even the
     # oracle's float32 and float64 products disagree on its sign)

@@ -1,5 +1,8 @@
 // Batched bf16 products of the local SGD step (bf16 operands, float32
-// accumulation) on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16).
+// accumulation) on the gfx950 matrix cores (v_mfma_f32_32x32x16_bf16): the
+// choice of the kernel, and the kernel for data rows that no 16-byte load fits
+// where they are not copied into aligned ones (the first layer's forward and
+// weight-gradient products).
 //
 // A workgroup of 4 waves owns a 128x128 output tile of one worker; each wave
 // owns a 64x64 quarter as 2x2 MFMA blocks (64 accumulator registers).  K is
@@ -7,11 +10,9 @@
 // the layout it has in memory.  An MFMA operand fragment is 16 bytes per
 // lane: one 16-byte LDS read from a K-contiguous tile ([outer][k]), two
 // transposing LDS reads (ds_read_b64_tr_b16) from a K-strided one
-// ([k][outer]: the N-contiguous weights of the input-gradient product and
-// both operands of the weight-gradient product).
+// ([k][outer]: both operands of the weight-gradient product).
 //
 // Epilogues: forward  H = bf16(relu(acc + b)) (logits stay float32);
-//            input gradient  dZ = bf16(acc * [H > 0]);
 //            weight gradient  W <- W - eta * acc on the float32 master, with
 //            the bf16 shadow of the new W written alongside (the operand of
 //            the next step's products); b <- b - eta * sum over rows of the
@@ -244,12 +245,6 @@ __device__ __forceinline__ void gemm_tile16(const GemmArgs& g, const int logical
         } else if (EPI == EPI_FWD_LINEAR) {
           reinterpret_cast<float*>(g.out)[(int64_t)worker * g.ostride + (int64_t)row * g.ldo + col] =
               v + g.bias[(int64_t)worker * g.bstride + col];
-        } else if (EPI == EPI_DX_MASK) {
-          const uint16_t hm =
-              reinterpret_cast<const uint16_t*>(g.mask)[(int64_t)worker * g.mstride + (int64_t)row * g.ldm + col];
-          const bool on = bf16_to_f32(hm) > 0.f;
-          reinterpret_cast<uint16_t*>(g.out)[(int64_t)worker * g.ostride + (int64_t)row * g.ldo + col] =
-              f32_to_bf16_rne(on ? v : 0.f);
         } else {  // EPI_DW_UPDATE
           const int64_t e = (int64_t)worker * g.pstride + (int64_t)row * g.ldw + col;
           const float step = g.adam.on ? adam_dir(v, g.adam.mw, g.adam.vw, e, g.adam, ac) : v;
@@ -282,18 +277,6 @@ __global__ __launch_bounds__(NT) void gemm_bf16_kernel(GemmArgs g) {
   gemm_tile16<A_KC, B_KC, EPI>(g, xcd_remap(blockIdx.x, tiles_of(g)), lds);
 }
 
-// Input-gradient tiles and weight-gradient tiles of one layer in one launch
-// (see the float32 version).
-__global__ __launch_bounds__(NT) void gemm_bf16_bwd_kernel(GemmArgs dx, GemmArgs dw, int n1, int n1pad) {
-  __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
-  const int pid = blockIdx.x;
-  if (pid < n1pad) {
-    if (pid < n1) gemm_tile16<true, false, EPI_DX_MASK>(dx, xcd_remap(pid, n1), lds);
-  } else {
-    gemm_tile16<false, false, EPI_DW_UPDATE>(dw, xcd_remap(pid - n1pad, tiles_of(dw)), lds);
-  }
-}
-
 template <bool A_KC, bool B_KC, int EPI>
 hipError_t go(const GemmArgs& g, hipStream_t s) {
   AGN_LAUNCH((gemm_bf16_kernel<A_KC, B_KC, EPI>), dim3(tiles_of(g)), dim3(NT), 0, s, g);
@@ -321,12 +304,10 @@ int small_tiles(int K) { return K < 2048 ? kSmallTiles : K < 4096 ? 168 : 144; }
 hipError_t launch_gemm_bf16_bwd(const GemmArgs& dx, const GemmArgs& dw, hipStream_t s) {
   if (dx.epi != EPI_DX_MASK || dw.epi != EPI_DW_UPDATE) return hipErrorInvalidValue;
   const bool dl = gemm_bf16_dl_ok(1, 0, dx) && gemm_bf16_dl_ok(0, 0, dw);
-  if (gemm_bf16_small_ok(dx) && gemm_bf16_small_ok(dw) && (!dl || tiles_of(dx) + tiles_of(dw) < kSmallTiles))
-    return launch_gemm_bf16_small_bwd(dx, dw, s);
-  if (dl) return launch_gemm_bf16_dl_bwd(dx, dw, s);
-  const int n1 = tiles_of(dx), n1pad = (n1 + kNumXcd - 1) / kNumXcd * kNumXcd;
-  AGN_LAUNCH(gemm_bf16_bwd_kernel, dim3(n1pad + tiles_of(dw)), dim3(NT), 0, s, dx, dw, n1, n1pad);
-  return hipGetLastError();
+  if (dl && tiles_of(dx) + tiles_of(dw) >= kSmallTiles) return launch_gemm_bf16_dl_bwd(dx, dw, s);
+  // (a hidden layer's operands are the context's own aligned buffers)
+  if (!gemm_bf16_small_ok(dx) || !gemm_bf16_small_ok(dw)) return hipErrorInvalidValue;
+  return launch_gemm_bf16_small_bwd(dx, dw, s);
 }
 
 hipError_t launch_gemm_bf16(int a_kc, int b_kc, const GemmArgs& g, hipStream_t s) {
@@ -336,7 +317,6 @@ hipError_t launch_gemm_bf16(int a_kc, int b_kc, const GemmArgs& g, hipStream_t s
   if (dl) return launch_gemm_bf16_dl(a_kc, b_kc, g, s);
   if (a_kc && b_kc && g.epi == EPI_FWD_RELU) return go<true, true, EPI_FWD_RELU>(g, s);
   if (a_kc && b_kc && g.epi == EPI_FWD_LINEAR) return go<true, true, EPI_FWD_LINEAR>(g, s);
-  if (a_kc && !b_kc && g.epi == EPI_DX_MASK) return go<true, false, EPI_DX_MASK>(g, s);
   if (!a_kc && !b_kc && g.epi == EPI_DW_UPDATE) return go<false, false, EPI_DW_UPDATE>(g, s);
   return hipErrorInvalidValue;
 }

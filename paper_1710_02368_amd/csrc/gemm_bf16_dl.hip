@@ -679,8 +679,6 @@ hipError_t launch_gemm_bf16_dl(int a_kc, int b_kc, const GemmArgs& g, hipStream_
     AGN_LAUNCH((gemm_bf16_dl_kernel<true, true, EPI_FWD_RELU>), grid, block, 0, s, g);
   else if (a_kc && b_kc && g.epi == EPI_FWD_LINEAR)
     AGN_LAUNCH((gemm_bf16_dl_kernel<true, true, EPI_FWD_LINEAR>), grid, block, 0, s, g);
-  else if (a_kc && !b_kc && g.epi == EPI_DX_MASK)
-    AGN_LAUNCH((gemm_bf16_dl_kernel<true, false, EPI_DX_MASK>), grid, block, 0, s, g);
   else if (!a_kc && !b_kc && g.epi == EPI_DW_UPDATE)
     AGN_LAUNCH((gemm_bf16_dl_kernel<false, false, EPI_DW_UPDATE>), grid, block, 0, s, g);
   else

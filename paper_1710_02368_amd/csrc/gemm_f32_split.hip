@@ -50,34 +50,25 @@ using Flat = SplitCfg<32, 64, 1, 1, 4, 1>;   // 32 x 64, four slices
 using Small = SplitCfg<32, 32, 1, 1, 4, 1>;  // 32 x 32, four slices: many tiles of a small product
 using MidW = SplitCfg<32, 32, 2, 2, 1, 2>;   // 64 x 64 as four waves of 32 x 32: weight gradients
 
+// LDS stages
 template <class Cfg>
-struct Stages {
-  static constexpr int A = 2, B = 2;
-};
+constexpr int kStages = 2;
 template <>
-struct Stages<Wide> {
-  static constexpr int A = 3, B = 3;
-};
+constexpr int kStages<Wide> = 3;
 template <>
-struct Stages<Small> {
-  static constexpr int A = 3, B = 3;
-};
+constexpr int kStages<Small> = 3;
 template <>
-struct Stages<Deep> {
-  static constexpr int A = 3, B = 3;
-};
+constexpr int kStages<Deep> = 3;
 template <>
-struct Stages<MidW> {
-  static constexpr int A = 3, B = 3;
-};
+constexpr int kStages<MidW> = 3;
 
 template <class Cfg>
-constexpr int lds_of() { return direct_lds_bytes<Cfg, Stages<Cfg>::A, Stages<Cfg>::B>(); }
+constexpr int lds_of() { return direct_lds_bytes<Cfg, kStages<Cfg>>(); }
 
 template <class Cfg, int EPI, int AW>
 __global__ __launch_bounds__(Cfg::NTH, 2) void split_fwd_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) char lds[lds_of<Cfg>()];
-  direct_tile<Cfg, Stages<Cfg>::A, Stages<Cfg>::B, false, true, true, EPI, false, AW, 4>(
+  direct_tile<Cfg, kStages<Cfg>, true, true, EPI, false, AW, 4>(
       g, xcd_remap(blockIdx.x, tiles_of<Cfg>(g)), lds);
 }
 
@@ -95,9 +86,9 @@ __global__ __launch_bounds__(CX::NTH, 2) void split_bwd_kernel(GemmArgs dx, Gemm
   const int pid = blockIdx.x;
   if (pid < n1pad) {
     if (pid < n1)
-      direct_tile<CX, Stages<CX>::A, Stages<CX>::B, false, true, false, EPI_DX_MASK, false>(dx, xcd_remap(pid, n1), lds);
+      direct_tile<CX, kStages<CX>, true, false, EPI_DX_MASK, false>(dx, xcd_remap(pid, n1), lds);
   } else {
-    direct_tile<CW, Stages<CW>::A, Stages<CW>::B, false, false, false, EPI_DW_UPDATE, ADAM>(
+    direct_tile<CW, kStages<CW>, false, false, EPI_DW_UPDATE, ADAM>(
         dw, xcd_remap(pid - n1pad, tiles_of<CW>(dw)), lds);
   }
 }
@@ -118,7 +109,7 @@ __global__ __launch_bounds__(Cfg::NTH, 2) void split_dw_kernel(GemmArgs dw, Head
       if (pid < units) head_dw_unit<HCM>(h, pid, reinterpret_cast<float*>(lds));
     return;
   }
-  direct_tile<Cfg, Stages<Cfg>::A, Stages<Cfg>::B, false, false, false, EPI_DW_UPDATE, ADAM, 4, BW>(
+  direct_tile<Cfg, kStages<Cfg>, false, false, EPI_DW_UPDATE, ADAM, 4, BW>(
       dw, xcd_remap(pid - upad, tiles_of<Cfg>(dw)), lds);
 }
 

@@ -199,10 +199,10 @@ struct DirectOperand {
   }
 };
 
-// LDS of a tile with NSA stages of operand A and NSB of operand B
-template <class Cfg, int NSA, int NSB>
+// LDS of a tile with NS stages
+template <class Cfg, int NS>
 constexpr int direct_lds_bytes() {
-  constexpr int stages = (NSA * Cfg::BM + NSB * Cfg::BN) * Cfg::BK * 4;
+  constexpr int stages = NS * (Cfg::BM + Cfg::BN) * Cfg::BK * 4;
   return stages > Cfg::EPI ? stages : Cfg::EPI;
 }
 
@@ -218,15 +218,12 @@ __device__ __forceinline__ void split_frag(const float (&x)[N][8], sp_bf16x8 (&f
   }
 }
 
-// One workgroup tile of one batched product.  Operand A (the activations or
-// gradients, shared by the tiles of a worker, in the L2) is loaded NSA - 1
-// steps ahead, B (the weights, streamed from memory) NSB - 1 steps.
-// EARLY: the epilogue's operands are loaded before everything else (weight
-// gradients: a few steps, then a block of the weights); otherwise behind the
-// last step's arrival, so that no step waits for them.
-template <class Cfg, int NSA, int NSB, bool EARLY, bool A_KC, bool B_KC, int EPI, bool ADAM, int AW = 4, int BW = 4>
+// One workgroup tile of one batched product.  The operands are loaded NS - 1
+// steps ahead, the epilogue's behind the last step's arrival, so that no step
+// waits for them.
+template <class Cfg, int NS, bool A_KC, bool B_KC, int EPI, bool ADAM, int AW = 4, int BW = 4>
 __device__ __forceinline__ void direct_tile(const GemmArgs& g, const int logical, char* lds) {
-  static_assert(NSA >= 2 && NSB >= NSA, "stages");
+  static_assert(NS >= 2, "stages");
   constexpr int BK = Cfg::BK, MB = Cfg::WTM / 32, NB = Cfg::WTN / 32;
   constexpr bool DW = EPI == EPI_DW_UPDATE;
   using OpA = DirectOperand<Cfg, Cfg::BM, Cfg::WTM, A_KC, AW>;
@@ -237,12 +234,13 @@ __device__ __forceinline__ void direct_tile(const GemmArgs& g, const int logical
   la.init(g.a, g.g, c.worker, c.m0, g.M, g.K, c.wave, c.lane, c.wm * Cfg::WTM, c.kw, g.zero);
   lb.init(g.b, g.g, c.worker, c.n0, g.N, g.K, c.wave, c.lane, c.wn * Cfg::WTN, c.kw, g.zero);
   const uint32_t lds0 = lds_off(lds);
-  constexpr int B0 = NSA * OpA::BYTES;  // operand B's stages follow operand A's
+  constexpr int B0 = NS * OpA::BYTES;  // operand B's stages follow operand A's
   const int nk = (g.K + BK - 1) / BK;
-  const auto fire_a = [&](int t, int stage) { la.fire(t * BK, lds0 + stage * OpA::BYTES); };
-  const auto fire_b = [&](int t, int stage) { lb.fire(t * BK, lds0 + B0 + stage * OpB::BYTES); };
+  const auto fire_step = [&](int t, int stage) {
+    la.fire(t * BK, lds0 + stage * OpA::BYTES);
+    lb.fire(t * BK, lds0 + B0 + stage * OpB::BYTES);
+  };
   SplitEpilogue<Cfg, EPI, ADAM> epi;
-  if (EARLY) epi.load(g, c);
 
   // bias gradient (first column tile of a weight gradient): sums of dZ over
   // this lane's k
@@ -257,13 +255,8 @@ __device__ __forceinline__ void direct_tile(const GemmArgs& g, const int logical
   const auto sweep = [&](auto f32) {
     constexpr bool F32 = decltype(f32)::value;
 #pragma unroll
-    for (int t = 0; t < NSB - NSA; ++t)
-      if (t < nk) fire_b(t, t);
-#pragma unroll
-    for (int t = 0; t < NSA - 1; ++t) {
-      if (t < nk) fire_a(t, t);
-      if (t + NSB - NSA < nk) fire_b(t + NSB - NSA, t + NSB - NSA);
-    }
+    for (int t = 0; t < NS - 1; ++t)
+      if (t < nk) fire_step(t, t);
     sp_f32x16 low[MB][NB];
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)
@@ -271,32 +264,29 @@ __device__ __forceinline__ void direct_tile(const GemmArgs& g, const int logical
       for (int bj = 0; bj < NB; ++bj)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[bi][bj][r] = low[bi][bj][r] = 0.f;
-    int sa = 0, sb = 0, na = NSA - 1, nb = NSB - 1;  // stages of the next step to read and to load
+    int st = 0, nxt = NS - 1;  // stages of the next step to read and to load
 
-    // Step t has landed: this wave's loads of it, then every wave's; and every
-    // wave is done reading the stages the next loads overwrite.  Turn u issues
-    // A(u + NSA - 1), then B(u + NSB - 1); step t's last load is followed by
-    // NSA - 2 whole turns, and by its own turn's B where that is a later step's
-    // (NSB > NSA).  At the end of K fewer follow, and all are waited for.
+    // Step t has landed: this wave's loads of it (those of the NS - 2 steps
+    // after it may be in flight; at the end of K fewer are, and all are waited
+    // for), then every wave's; and every wave is done reading the stage the
+    // next loads overwrite.
     const auto arrive = [&](int t) {
-      constexpr int YOUNGER = (NSA - 2) * (OpA::LPS + OpB::LPS) + (NSB > NSA ? OpB::LPS : 0);
-      if (YOUNGER < 64 && t + NSB - 2 < nk)
+      constexpr int YOUNGER = (NS - 2) * (OpA::LPS + OpB::LPS);
+      if (YOUNGER < 64 && t + NS - 2 < nk)
         wait_vm<YOUNGER < 64 ? YOUNGER : 0>();
       else
         wait_vm<0>();
       wait_lgkm0();
       barrier();
-      if (t + NSA - 1 < nk) fire_a(t + NSA - 1, na);
-      if (t + NSB - 1 < nk) fire_b(t + NSB - 1, nb);
-      na = na + 1 == NSA ? 0 : na + 1;
-      nb = nb + 1 == NSB ? 0 : nb + 1;
+      if (t + NS - 1 < nk) fire_step(t + NS - 1, nxt);
+      nxt = nxt + 1 == NS ? 0 : nxt + 1;
       // the epilogue's operands come in behind the last step (the waits above
       // do not count them)
-      if (!F32 && !EARLY && t + 1 == nk) epi.load(g, c);
+      if (!F32 && t + 1 == nk) epi.load(g, c);
     };
     for (int t = 0; t < nk; ++t) {
       arrive(t);
-      const char *sta = lds + sa * OpA::BYTES, *stb = lds + B0 + sb * OpB::BYTES;
+      const char *sta = lds + st * OpA::BYTES, *stb = lds + B0 + st * OpB::BYTES;
 #pragma unroll
       for (int s = 0; s < Cfg::SL; ++s) {
         float xa[MB][8], xb[NB][8];
@@ -323,8 +313,7 @@ __device__ __forceinline__ void direct_tile(const GemmArgs& g, const int logical
           split_mfma<MB, NB>(a, b, acc, low);
         }
       }
-      sa = sa + 1 == NSA ? 0 : sa + 1;
-      sb = sb + 1 == NSB ? 0 : sb + 1;
+      st = st + 1 == NS ? 0 : st + 1;
     }
 #pragma unroll
     for (int bi = 0; bi < MB; ++bi)

@@ -91,8 +91,8 @@ struct SplitCfg {
   static constexpr int BM = WTM * WGM, BN = WTN * WGN, BK = 16 * KW * SL, NTH = 64 * WGM * WGN * KW;
   static constexpr int ELD = BN;               // row stride (floats) of the epilogue tile
   static constexpr int EPI = KW * BM * ELD * 4;
-  static constexpr int NC = (BM * BN / 4 + NTH - 1) / NTH;  // epilogue chunks of 4 outputs per thread
-  static_assert(NC == 1 || BM * BN % (4 * NTH) == 0, "epilogue chunks");
+  static constexpr int NC = BM * BN / 4 / NTH;  // epilogue chunks of 4 outputs per thread
+  static_assert(BM * BN % (4 * NTH) == 0, "whole epilogue chunks per thread");
 };
 
 // element (outer o, k) of an operand straight from memory
@@ -119,10 +119,8 @@ template <class Cfg>
 struct SplitCoord {
   int tid, lane, wave, kw, wn, wm, li, lh, worker, m0, n0;
   // this thread's epilogue chunks: 4 outputs at column ec of rows m0 + er0 +
-  // i*ERS (threads past the tile's last chunk repeat its last row, storing
-  // nothing)
+  // i*ERS
   int ecl, ec, er0;
-  bool mine;
   static constexpr int ERS = Cfg::NTH / (Cfg::BN / 4);
 
   __device__ __forceinline__ SplitCoord(const GemmArgs& g, int logical) {
@@ -145,8 +143,7 @@ struct SplitCoord {
     n0 = tj * Cfg::BN;
     ecl = 4 * (tid % (Cfg::BN / 4));
     ec = n0 + ecl;
-    er0 = min(tid / (Cfg::BN / 4), Cfg::BM - 1);
-    mine = tid / (Cfg::BN / 4) < Cfg::BM;
+    er0 = tid / (Cfg::BN / 4);
   }
 };
 
@@ -202,7 +199,7 @@ struct SplitEpilogue {
   // (first column tile of a weight gradient)
   __device__ __forceinline__ void store(const GemmArgs& g, const SplitCoord<Cfg>& c, const sp_f32x4 (&v)[NC], float gb) {
     if (!DW) {
-      if (c.mine && c.ec < g.ldo) {  // (columns past N are stored as zeros: the row padding stays zero)
+      if (c.ec < g.ldo) {  // (columns past N are stored as zeros: the row padding stays zero)
         const int64_t e0 = c.worker * g.ostride + c.ec;
 #pragma unroll
         for (int i = 0; i < NC; ++i) {
@@ -230,7 +227,7 @@ struct SplitEpilogue {
     }
     const AdamCoef ac = ADAM ? adam_coef(g.g, g.adam) : AdamCoef{1.f, 1.f};
     const int64_t wo = c.worker * g.pstride;
-    if (c.mine && c.ec < g.N) {
+    if (c.ec < g.N) {
 #pragma unroll
       for (int i = 0; i < NC; ++i) {
         const int64_t row = c.m0 + c.er0 + i * c.ERS;

@@ -38,6 +38,8 @@ sys.path.insert(0, ROOT)
 METRIC = "worker-samples/sec per AGN round on 1 MI355X; MFMA util % + commit HBM GB/s"
 PEAK_HBM_GBS = 8000.0
 PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2516.6}   # dense MFMA peaks of MI355X
+SPLIT_TFLOPS = PEAK_TFLOPS["bf16"] / 6           # float32 products done as six bf16 products
+STRIP_MIN_GROUPS = 1024                          # (kStripMinGroups of gemm_f32_strip.hip)
 CLASSES = ["fwd", "output", "output_dw", "bwd", "dw_first", "commit"]
 
 
@@ -52,7 +54,38 @@ def class_work(agn, g):
     return out
 
 
-def bound_of(w, dtype):
+def class_peak(wl, c):
+    """The MFMA rate that bounds a class's products (TFLOP/s): in float32 that
+    of the split products, or the float32 MFMA's for the strip kernels and the
+    output layer; a class whose layers differ gets the rate of its flops at
+    their layers' rates."""
+    if wl.dtype != "fp32":
+        return PEAK_TFLOPS[wl.dtype]
+    if c not in ("fwd", "eval", "bwd", "dw_first"):
+        return PEAK_TFLOPS["fp32"]
+
+    def strips(width, other):
+        return (wl.m <= 128 and width % 4 == 0 and other % 4 == 0
+                and wl.n * -(-width // 64) >= STRIP_MIN_GROUPS)
+
+    d = wl.dims
+    if c == "dw_first":
+        return PEAK_TFLOPS["fp32"] if strips(d[1], d[0]) else SPLIT_TFLOPS
+    if c == "bwd":
+        layers = range(1, wl.num_layers if d[-1] > 32 else wl.num_layers - 1)
+        macs = [d[l] * d[l + 1] for l in layers]
+        cost = [d[l] * d[l + 1] / (PEAK_TFLOPS["fp32"] if strips(d[l], d[l + 1]) else SPLIT_TFLOPS) for l in layers]
+        return sum(macs) / sum(cost) if macs else SPLIT_TFLOPS
+    return SPLIT_TFLOPS
+
+
+def round_peak(wl, work):
+    """The MFMA rate that bounds a round: its classes' flops at their rates."""
+    flops = {c: w["flops"] for c, w in work.items() if w["flops"] > 0}
+    return sum(flops.values()) / sum(f / class_peak(wl, c) for c, f in flops.items())
+
+
+def bound_of(w, peak):
     """A class of matrix products is MFMA-bound when its algorithmic
     intensity reaches the ridge point (peak FLOP/s over peak bytes/s), else
     bound by HBM; classes without products are HBM-bound."""
@@ -60,7 +93,7 @@ def bound_of(w, dtype):
         return "hbm"
     if w["bytes"] <= 0:
         return "mfma"
-    ridge = PEAK_TFLOPS[dtype] * 1e12 / (PEAK_HBM_GBS * 1e9)
+    ridge = peak * 1e12 / (PEAK_HBM_GBS * 1e9)
     return "mfma" if w["flops"] / w["bytes"] >= ridge else "hbm"
 
 
@@ -162,13 +195,13 @@ def measure_eval(agn, g, wl, xh, yh, Xh, yh_host, reps=20, cpu=True):
     agn.agn_set_kernel_timing(g.ctx, k, False)
     flops, nbytes = agn.agn_kernel_class_work(g.ctx, k)
     per_call_s = ms * 1e-3 / kt
-    dtype = wl.dtype
+    peak = class_peak(wl, "eval")
     tf = flops / per_call_s / 1e12
     out = {"rows": rows, "rows_per_s": round(rows / dt, 1), "ms_per_eval": round(dt * 1e3, 4),
            "mean_loss": round(res[0], 6), "accuracy": res[1],
-           "roofline": {"bound": bound_of({"flops": flops, "bytes": nbytes}, dtype),
-                        "achieved": round(tf, 3), "peak": PEAK_TFLOPS[dtype], "unit": "TFLOP/s",
-                        "frac": round(tf / PEAK_TFLOPS[dtype], 4), "kernel_class": "eval",
+           "roofline": {"bound": bound_of({"flops": flops, "bytes": nbytes}, peak),
+                        "achieved": round(tf, 3), "peak": round(peak, 1), "unit": "TFLOP/s",
+                        "frac": round(tf / peak, 4), "kernel_class": "eval",
                         "launches_per_eval": cnt // kt,
                         "avg_launch_us": round(ms * 1e3 / max(cnt, 1), 2),
                         "algorithmic_per_eval": flops}}
@@ -501,7 +534,7 @@ def main():
         e = {"ms_per_round": round(per_round_s * 1e3, 4), "launches_per_round": cnt // prof_rounds}
         if work[c]["flops"] > 0:
             e["TFLOP/s"] = round(work[c]["flops"] / per_round_s / 1e12, 2)
-            e["mfma_frac"] = round(work[c]["flops"] / per_round_s / 1e12 / PEAK_TFLOPS[wl.dtype], 4)
+            e["mfma_frac"] = round(work[c]["flops"] / per_round_s / 1e12 / class_peak(wl, c), 4)
         if work[c]["bytes"] > 0:
             e["GB/s"] = round(work[c]["bytes"] / per_round_s / 1e9, 1)
             e["hbm_frac"] = round(work[c]["bytes"] / per_round_s / 1e9 / PEAK_HBM_GBS, 4)
@@ -540,14 +573,15 @@ def main():
 
     value = args.steps * wl.worker_samples_per_round / dt
     wd = work[dominant]
-    bound = bound_of(wd, wl.dtype)
+    peak = class_peak(wl, dominant)
+    bound = bound_of(wd, peak)
     launches_per_round = max(dom_cnt, 1) / kt_rounds
     avg_s = dom_ms * 1e-3 / max(dom_cnt, 1)
     if bound == "mfma":
         per_launch = wd["flops"] / launches_per_round
         achieved = per_launch / avg_s / 1e12
-        roof = {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_TFLOPS[wl.dtype],
-                "unit": "TFLOP/s", "frac": round(achieved / PEAK_TFLOPS[wl.dtype], 4)}
+        roof = {"bound": "mfma", "achieved": round(achieved, 3), "peak": round(peak, 1),
+                "unit": "TFLOP/s", "frac": round(achieved / peak, 4)}
     else:
         per_launch = wd["bytes"] / launches_per_round
         achieved = per_launch / avg_s / 1e9
@@ -578,7 +612,7 @@ def main():
                             "copy_ceiling": {"achieved": round(copy_gbs, 1), "unit": "GB/s",
                                              "kind": "device-to-device copy of the same bytes, same run"},
                             "frac_of_copy": round(commit_gbs / copy_gbs, 4)},
-        "round_mfma_util": round(wl.flops_per_round / (dt / args.steps) / 1e12 / PEAK_TFLOPS[wl.dtype], 4),
+        "round_mfma_util": round(wl.flops_per_round / (dt / args.steps) / 1e12 / round_peak(wl, work), 4),
         "kernels": breakdown,
     }
     if ev is not None:

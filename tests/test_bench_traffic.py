@@ -56,3 +56,27 @@ def test_traffic_classes():
     assert bench.traffic_class("void agn::(anonymous namespace)::head_dw_kernel<10>(x)") == "output_dw"
     assert bench.traffic_class("void agn::(anonymous namespace)::head_kernel<10, 16, false>(x)") == "output"
     assert bench.traffic_class("__amd_rocclr_fillBufferAligned") is None
+
+
+def test_class_peaks():
+    """Split products are held against a sixth of the bf16 rate, the strip
+    kernels against the float32 MFMA's."""
+    import os
+    import re
+
+    import workloads as W
+    src = os.path.join(os.path.dirname(os.path.abspath(bench.__file__)), "paper_1710_02368_amd", "csrc",
+                       "gemm_f32_strip.hip")
+    with open(src) as fh:
+        assert int(re.search(r"kStripMinGroups = (\d+)", fh.read()).group(1)) == bench.STRIP_MIN_GROUPS
+    f32, bf16 = bench.PEAK_TFLOPS["fp32"], bench.PEAK_TFLOPS["bf16"]
+    n8, n40, wide = W.workload("mlp1000_n8"), W.workload("mlp2000_n40"), W.workload("wide_bf16")
+    for c in ("fwd", "bwd", "dw_first", "eval"):
+        assert bench.class_peak(n8, c) == bf16 / 6
+        assert bench.class_peak(wide, c) == bf16
+    assert bench.class_peak(n40, "fwd") == bf16 / 6
+    assert abs(bench.class_peak(n40, "bwd") / f32 - 1) < 1e-12 and bench.class_peak(n40, "dw_first") == f32
+    assert bench.class_peak(n8, "output") == f32
+    assert bench.round_peak(n8, {"fwd": {"flops": 3.0}, "commit": {"flops": 0.0}}) == bf16 / 6
+    mixed = bench.round_peak(n40, {"fwd": {"flops": 1.0}, "bwd": {"flops": 1.0}})
+    assert abs(mixed - 2.0 / (6 / bf16 + 1 / f32)) < 1e-9

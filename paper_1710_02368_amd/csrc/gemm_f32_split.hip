@@ -136,8 +136,10 @@ hipError_t go_fwd(const GemmArgs& g, hipStream_t s) {
 //   24 x 128 x 1000 x 784        768           50.0          47.9
 //   28 x 128 x 1000 x 784        896           56.4          56.1
 // (Deep's 96 KB of LDS leave one workgroup per compute unit, so it ends at a
-// tile per unit.)
-constexpr int kFlatTiles = 200, kDeepTiles = 256, kMidTiles = 700;
+// tile per unit.)  Data rows that are loaded in single floats need the more
+// waves of Flat: 6 x 128 x 1000 x 785, 192 tiles, Small 37.4, Flat 35.2; 8 x,
+// 256, Small 53.9, Flat 35.8, Deep 52.3.
+constexpr int kFlatTiles = 200, kFlatTilesWords = 128, kDeepTiles = 256, kMidTiles = 700;
 // ... and from this many 128 x 64 tiles on, a tile holds a worker's whole
 // mini-batch and reads each weight once (Wide against Mid: 40 x 128 x 2000 x
 // 784, 1280 tiles, 119 us both, and 255 against 267 at 2000 x 2000; 32 x 128 x
@@ -152,8 +154,8 @@ hipError_t fwd(const GemmArgs& g, hipStream_t s) {
   if (g.batch > 1 && g.M > 64 && tiles_of<Wide>(g) >= kWideTiles) return go_fwd<Wide, EPI>(g, s);
   const int t = tiles_of<Mid>(g);
   if (t >= kMidTiles) return go_fwd<Mid, EPI>(g, s);
-  if (t < kFlatTiles) return go_fwd<Small, EPI>(g, s);
-  return t <= kDeepTiles ? go_fwd<Deep, EPI>(g, s) : go_fwd<Flat, EPI>(g, s);
+  if (t < (g.a.vec ? kFlatTiles : kFlatTilesWords)) return go_fwd<Small, EPI>(g, s);
+  return t <= kDeepTiles && g.a.vec ? go_fwd<Deep, EPI>(g, s) : go_fwd<Flat, EPI>(g, s);
 }
 
 template <class CX, class CW>

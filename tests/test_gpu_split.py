@@ -19,7 +19,6 @@ CASES = {
     "flat_midw_unaligned": ((131, 514, 66, 12), 16, 70, 16 * 90),
     "flat_bwd": ((64, 260, 514, 10), 16, 70, 16 * 90),          # 32 x 64 input gradient beside 64 x 64 weight tiles
     "deep": ((132, 450, 66, 10), 16, 70, 16 * 90),              # 64 x 64 forward, three stages
-    "deep_unaligned": ((131, 450, 66, 10), 16, 70, 16 * 90),
     "mid": ((68, 385, 33, 10), 40, 130, 40 * 200),              # 64 x 64 forward
     "wide": ((36, 700, 33, 10), 48, 130, 48 * 200),             # 128 x 64 forward, the second row tile of 2 rows
     "wide_unaligned": ((37, 700, 33, 10), 48, 130, 48 * 200),

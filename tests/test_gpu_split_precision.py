@@ -38,12 +38,14 @@ def tiles(n, rows, cols, bm=64, bn=64):
     return n * -(-rows // bm) * -(-cols // bn)
 
 
-def forward_shape(n, m, out):
+def forward_shape(n, m, out, inp):
     if n > 1 and m > 64 and tiles(n, m, out, 128) >= rule("kWideTiles"):
         return "wide"
     t = tiles(n, m, out)
     if t >= rule("kMidTiles"):
         return "mid"
+    if inp % 4:  # (single-float loads)
+        return "small" if t < rule("kFlatTilesWords") else "flat"
     return "small" if t < rule("kFlatTiles") else "deep" if t <= rule("kDeepTiles") else "flat"
 
 
@@ -107,9 +109,8 @@ TWO_LAYERS = {
     "small_linear": ((64, 96, 40), 3, 32, "small", "small"),         # (logits by the split product)
     "small_full": ((132, 514, 10), 16, 64, "small", "midw"),
     "deep": ((132, 900, 10), 16, 64, "deep", "midw"),
-    "deep_unaligned": ((131, 900, 10), 16, 64, "deep", "midw"),
     "flat": ((132, 1100, 10), 16, 64, "flat", "midw"),
-    "flat_unaligned": ((131, 1100, 10), 16, 64, "flat", "midw"),
+    "flat_unaligned": ((131, 514, 10), 16, 64, "flat", "midw"),
     "mid": ((68, 580, 10), 40, 128, "mid", "midw"),
     "wide": ((36, 900, 10), 40, 256, "wide", "midw"),
     "wide_unaligned": ((37, 900, 10), 40, 256, "wide", "midw"),
@@ -127,7 +128,7 @@ TWO_LAYER_RANGES = {
 @pytest.mark.parametrize("case", TWO_LAYERS)
 def test_forward_and_first_layer(case, rng_name):
     dims, n, m, fwd, dw = TWO_LAYERS[case]
-    assert (forward_shape(n, m, dims[1]), dw_shape(n, dims[1], dims[0])) == (fwd, dw)
+    assert (forward_shape(n, m, dims[1], dims[0]), dw_shape(n, dims[1], dims[0])) == (fwd, dw)
     ex, e0, e1, redo_fwd, redo_dw = TWO_LAYER_RANGES[rng_name]
     print(case, rng_name, dims, n, m, flush=True)
     rng = np.random.default_rng(5)

@@ -26,8 +26,9 @@
 // products (5.5 per element without the factor) overlap with MFMAs, which
 // those do not, and still measured slower (forward product 40 x 128 x 2000 x
 // 2000: 271 against 256 us; weight gradient 547 against 518).  The factor
-// costs a round of 8 x 784-1000-1000-10, m = 128 1897 against 1849 us, of 20
-// workers 4098 against 3974, of 10 x 784-512-256-10, m = 64 573 against 553.
+// cost a round of 8 x 784-1000-1000-10, m = 128 1897 against 1849 us when it
+// came in, of 20 workers 4098 against 3974, of 10 x 784-512-256-10, m = 64 573
+// against 553.
 //
 // Infinities: inf - inf in the split makes NaN where the float32 product
 // would keep an infinity, and results of 2^96 and more (operands of 2^111)
@@ -303,9 +304,10 @@ __device__ __forceinline__ void split_gather(const SplitCoord<Cfg>& c, float* et
 // that has diverged to NaN run at their ordinary speed; NaNs are looked for
 // at kNanProbes k of every row and column (the update of a layer spreads one
 // over a whole row of its weights; a NaN that is not found costs the tile its
-// second pass, nothing else).  8 x 784-1000-1000-10, m = 128, us per round:
-// finite 1979; all weights NaN 2035; one weight in 5488 NaN 2528 (with every
-// such tile computed again by loads straight from memory: 4676 in both).
+// second pass, nothing else).  8 x 784-1000-1000-10, m = 128, us per round
+// that is waited for: finite 1960; all weights NaN 2050; one weight in 5488 NaN
+// 2357 (with every such tile computed again by loads straight from memory:
+// 4676 in both).
 // lds is free when this returns.
 constexpr int kNanProbes = 16;
 

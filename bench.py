@@ -214,7 +214,7 @@ def measure_eval(agn, g, wl, xh, yh, Xh, yh_host, reps=20, cpu=True):
         from oracle import he_normal_init
         params = he_normal_init(wl.dims, wl.seed)
         t0 = time.perf_counter()
-        evaluate(params, Xh, yh_host, bf16=dtype == "bf16")
+        evaluate(params, Xh, yh_host, bf16=wl.dtype == "bf16")
         ct = time.perf_counter() - t0
         out["cpu_baseline"] = {"value": round(rows / ct, 1), "unit": "rows/s", "cores": int(cores),
                                "kind": "oracle",

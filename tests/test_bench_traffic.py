@@ -80,3 +80,26 @@ def test_class_peaks():
     assert bench.round_peak(n8, {"fwd": {"flops": 3.0}, "commit": {"flops": 0.0}}) == bf16 / 6
     mixed = bench.round_peak(n40, {"fwd": {"flops": 1.0}, "bwd": {"flops": 1.0}})
     assert abs(mixed - 2.0 / (6 / bf16 + 1 / f32)) < 1e-9
+
+
+def test_evaluation_record(monkeypatch):
+    """The evaluation's part of the record, with the oracle's time beside it,
+    from a library that does nothing."""
+    import types
+
+    import numpy as np
+    import torch
+
+    import workloads as W
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda: None)
+    wl = W.small_workload("record", (6, 5, 3), 2, 1, 4, 0.1, 1, 20)
+    X, y = W.make_data(wl)
+    lib = types.SimpleNamespace(
+        KERNEL_CLASSES={"eval": 6}, agn_evaluate=lambda *a, **k: None, agn_set_kernel_timing=lambda *a: None,
+        agn_kernel_timing=lambda *a: (5.0, 15), agn_kernel_class_work=lambda *a: (4.0e9, 1.0e6))
+    ctx = types.SimpleNamespace(ctx=None, dtype=0, evaluate=lambda *a: (1.25, 0.5, 10))
+    out = bench.measure_eval(lib, ctx, wl, torch.from_numpy(X), torch.from_numpy(np.asarray(y)), X, y)
+    r = out["roofline"]
+    assert (r["bound"], r["achieved"], r["launches_per_eval"], r["avg_launch_us"]) == ("mfma", 4.0, 3, 333.33)
+    assert r["frac"] == round(4.0 / bench.SPLIT_TFLOPS, 4)
+    assert out["cpu_baseline"]["kind"] == "oracle" and out["cpu_baseline"]["value"] > 0
